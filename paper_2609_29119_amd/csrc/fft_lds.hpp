@@ -22,10 +22,16 @@
 #include "radix_consts.hpp"
 #include "tables.hpp"
 
+// A sum of products is fused only where it is written as fmaf: a transform is
+// instantiated in many kernels (block sizes, elements per thread) and gives the
+// same bits in each, so results do not depend on the batch, which picks among
+// them. Left to itself the compiler may fuse a b - c d either way round.
+#pragma clang fp contract(off)
+
 namespace nsg {
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x));
 }
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
@@ -44,6 +50,37 @@ __device__ __forceinline__ int stage_tid() {
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
     return t;
+}
+
+// Threads of a workgroup that take part in its transform: the block size of a
+// kernel whose launch has one workgroup shape, or a wave-uniform count of a
+// work item (a multiple of 64; the workgroup's other waves have ended).
+template <int N> struct FixedNt {
+    __device__ __forceinline__ constexpr operator int() const { return N; }
+};
+struct ItemNt {
+    int n;
+    __device__ __forceinline__ operator int() const { return n; }
+};
+
+// A stage record in registers: rec_fetch issues its read, rec_uniform moves it
+// to scalar registers. The record of the next stage is read while the current
+// one writes its results, so a stage does not start with an LDS round trip.
+struct RawRec {
+    int4 a;
+    float2 r;
+};
+struct StageRec {
+    int R, Ns, m, stoff;
+    float rns, rh;
+};
+__device__ __forceinline__ RawRec rec_fetch(const FftStage* st) {
+    return RawRec{make_int4(st->R, st->Ns, st->m, st->stoff), make_float2(st->rcp_ns, st->rcp_h)};
+}
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float unif(float v) { return __int_as_float(uni(__float_as_int(v))); }
+__device__ __forceinline__ StageRec rec_uniform(const RawRec& r) {
+    return StageRec{uni(r.a.x), uni(r.a.y), uni(r.a.z), uni(r.a.w), unif(r.r.x), unif(r.r.y)};
 }
 
 // Exact quotient and remainder of 0 <= x < 2^22 by 0 < d < 2^22 through the
@@ -121,13 +158,16 @@ template <> struct Dft<8> {
         Dft<4>::run(e);
         Dft<4>::run(o);
         // o[q] *= exp(-2 pi i q / 8)
-        const float2 o1 = make_float2(r * (o[1].x + o[1].y), r * (o[1].y - o[1].x));
+        // (the factor r is fused into the sums)
+        const float2 o1 = make_float2(o[1].x + o[1].y, o[1].y - o[1].x);
         const float2 o2 = mul_mi(o[2]);
-        const float2 o3 = make_float2(r * (o[3].y - o[3].x), -r * (o[3].x + o[3].y));
+        const float2 o3 = make_float2(o[3].y - o[3].x, -o[3].x - o[3].y);
         v[0] = cadd(e[0], o[0]); v[4] = csub(e[0], o[0]);
-        v[1] = cadd(e[1], o1);   v[5] = csub(e[1], o1);
+        v[1] = make_float2(fmaf(r, o1.x, e[1].x), fmaf(r, o1.y, e[1].y));
+        v[5] = make_float2(fmaf(-r, o1.x, e[1].x), fmaf(-r, o1.y, e[1].y));
         v[2] = cadd(e[2], o2);   v[6] = csub(e[2], o2);
-        v[3] = cadd(e[3], o3);   v[7] = csub(e[3], o3);
+        v[3] = make_float2(fmaf(r, o3.x, e[3].x), fmaf(r, o3.y, e[3].y));
+        v[7] = make_float2(fmaf(-r, o3.x, e[3].x), fmaf(-r, o3.y, e[3].y));
     }
 };
 
@@ -155,8 +195,9 @@ template <int R> struct DftPrime {
             for (int r = 1; r <= h; ++r) {
                 const float c = RootR<R>::re(r * q);
                 const float sn = -RootR<R>::im(r * q);
-                A.x += s[r].x * c; A.y += s[r].y * c;
-                B.x += d[r].x * sn; B.y += d[r].y * sn;
+                A.x = fmaf(s[r].x, c, A.x); A.y = fmaf(s[r].y, c, A.y);
+                if (r == 1) B = cscale(d[r], sn);
+                else { B.x = fmaf(d[r].x, sn, B.x); B.y = fmaf(d[r].y, sn, B.y); }
             }
             v[q] = make_float2(A.x + B.y, A.y - B.x);       // A - i B
             v[R - q] = make_float2(A.x - B.y, A.y + B.x);   // A + i B
@@ -164,6 +205,15 @@ template <int R> struct DftPrime {
         v[0] = x0;
     }
 };
+
+// v omega_R^t for a t known after unrolling; quarter turns cost no product.
+template <int R> __device__ __forceinline__ float2 mul_root(float2 v, int t) {
+    t %= R;
+    if (4 * t == R) return mul_mi(v);
+    if (2 * t == R) return make_float2(-v.x, -v.y);
+    if (4 * t == 3 * R) return make_float2(-v.y, v.x);
+    return cmul(v, make_float2(RootR<R>::re(t), RootR<R>::im(t)));
+}
 
 // R = A B by one Cooley-Tukey step in registers: input r = A b + a, output
 // q = q1 + B q2; B-point DFTs over b, twiddles omega_R^{a q1}, A-point DFTs
@@ -182,7 +232,7 @@ template <int A, int B> struct DftComposite {
         for (int a = 1; a < A; ++a)
 #pragma unroll
             for (int q1 = 1; q1 < B; ++q1)
-                y[a][q1] = cmul(y[a][q1], make_float2(RootR<R>::re(a * q1), RootR<R>::im(a * q1)));
+                y[a][q1] = mul_root<R>(y[a][q1], a * q1);
 #pragma unroll
         for (int q1 = 0; q1 < B; ++q1) {
             float2 z[A];
@@ -214,43 +264,81 @@ template <> struct Dft<16> { __device__ __forceinline__ static void run(float2* 
 // Butterfly jj of sequence t reads in[jj + r m] (m = n/R), multiplies input r
 // by omega_{Ns R}^{r k} (k = jj mod Ns, table tws[k (R-1) + r - 1]), applies
 // the length-R DFT, and after a barrier writes out[(jj - k) R + k + r Ns].
-// The twiddles omega_{Ns R}^{r k} come precomputed per stage (tws).
-template <int R, int NT, int EPT>
-__device__ __forceinline__ void stage_fixed(float2* buf, int n, int S, int lgnb, int Ns, float rns,
-                                            const float2* __restrict__ tws) {
+// The twiddles omega_{Ns R}^{r k} come precomputed per stage (tws); their
+// reads are issued before the LDS reads, so the two round trips overlap.
+// PRE: pre non-null makes the first stage (Ns = 1) read conj(in K) with
+// K[i] = pre[i] in the place of in (Bluestein's product between its transforms).
+//
+// What bounds it: with few workgroups a stage is one wave's serial chain (a
+// vector instruction every 4 cycles, LDS and cache round trips, two barriers);
+// with many, the vector instructions. Stamped with the cycle counter, a stage
+// took 2,000 to 2,600 cycles: about 350 to find its radix and divisors, 450 to
+// 900 waiting for twiddles read after the inputs, 350 in the DFT; each
+// transform also spent 200 scalar instructions on n / R for every radix.
+// Stage records with every divisor worked out by the plan, read one stage
+// ahead, twiddle reads ahead of the input reads and Bluestein's product
+// inside the second transform took the smallest analysis (1 x 16,384) from
+// 32.8 to 28.5 us, 3 x 50,274 from 119 to 107.5 us a round trip and 128 x
+// 88,200 from 377 to 354 us.
+template <int R, int EPT, bool PRE, class NT>
+__device__ __forceinline__ void stage_fixed(float2* buf, NT nt, const StageRec& st, int S, int lgnb,
+                                            const float2* __restrict__ tws, const float2* __restrict__ pre,
+                                            const FftStage* next, RawRec& nraw) {
     constexpr int BPT = (EPT + R - 1) / R;
     const int tid = stage_tid();
-    const int m = n / R;
+    const int m = st.m, Ns = st.Ns;
     const int total = m << lgnb;
     const int nbm = (1 << lgnb) - 1;
     const int mS = __mul24(m, S), NsS = __mul24(Ns, S);
-    const Div dns = mkdiv(Ns, rns);
+    const Div dns = mkdiv(Ns, st.rns);
     float2 v[BPT][R];
     int ob[BPT];
 #pragma unroll
     for (int b = 0; b < BPT; ++b) {
-        const int j = tid + b * NT;
+        const int j = tid + b * nt;
         ob[b] = -1;
         if (j < total) {
             const int t = j & nbm, jj = j >> lgnb;
-            int k = 0;
-            if (Ns > 1) qdiv(jj, dns, k);
             int a = __mul24(jj, S) + t;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                v[b][r] = buf[a];
-                a += mS;
-            }
             if (Ns > 1) {
-                const float2* w = tws + __mul24(k, R - 1);
+                int k;
+                qdiv(jj, dns, k);
+                float2 w[R];
+                const float2* wp = tws + __mul24(k, R - 1);
 #pragma unroll
-                for (int r = 1; r < R; ++r) v[b][r] = cmul(v[b][r], w[r - 1]);
+                for (int r = 1; r < R; ++r) w[r] = wp[r - 1];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    v[b][r] = buf[a];
+                    a += mS;
+                }
+#pragma unroll
+                for (int r = 1; r < R; ++r) v[b][r] = cmul(v[b][r], w[r]);
+                ob[b] = __mul24(__mul24(jj - k, R) + k, S) + t;
+            } else {
+                if (PRE && pre) {
+                    float2 w[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) w[r] = at32(pre + r * m, static_cast<uint32_t>(jj));
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        v[b][r] = conjf2(cmul(buf[a], w[r]));
+                        a += mS;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        v[b][r] = buf[a];
+                        a += mS;
+                    }
+                }
+                ob[b] = __mul24(__mul24(jj, R), S) + t;
             }
             Dft<R>::run(v[b]);
-            ob[b] = __mul24(__mul24(jj - k, R) + k, S) + t;
         }
     }
     __syncthreads();
+    nraw = rec_fetch(next);
 #pragma unroll
     for (int b = 0; b < BPT; ++b) {
         if (ob[b] >= 0) {
@@ -269,26 +357,26 @@ __device__ __forceinline__ void stage_fixed(float2* buf, int n, int S, int lgnb,
 // (r, R - r), r = 1..h, of every butterfly is multiplied by its stage twiddle
 // and replaced in place by s_r = y_r + y_{R-r} (at r) and d_r = y_r - y_{R-r}
 // (at R - r). Input 0 carries no twiddle.
-template <int NT>
-__device__ __forceinline__ void prime_fold(float2* buf, int n, int S, int lgnb, int Ns, int R, float rns,
-                                           float rh, const float2* __restrict__ tws) {
+template <class NT>
+__device__ __forceinline__ void prime_fold(float2* buf, NT nt, const StageRec& st, int S, int lgnb,
+                                           const float2* __restrict__ tws) {
     const int tid = stage_tid();
-    const int m = n / R;
+    const int m = st.m, R = st.R, Ns = st.Ns;
     const int h = (R - 1) >> 1;
     const int nbm = (1 << lgnb) - 1;
     const int mS = __mul24(m, S);
     const int totb = m << lgnb;
-    const Div dns = mkdiv(Ns, rns), dh = mkdiv(h, rh);
+    const Div dns = mkdiv(Ns, st.rns), dh = mkdiv(h, st.rh);
     const int total = __mul24(totb, h);
     // four pairs at a time, all twiddle reads issued first
     constexpr int U = 4;
-    for (int e0 = tid; e0 < total; e0 += U * NT) {
+    for (int e0 = tid; e0 < total; e0 += U * nt) {
         int ia[U], ic[U];
         float2 wa[U], wc[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             int r1;
-            const int j = qdiv(min(e0 + u * NT, total - 1), dh, r1);
+            const int j = qdiv(min(e0 + u * nt, total - 1), dh, r1);
             const int r = r1 + 1;
             const int jj = j >> lgnb;
             const int a0 = __mul24(jj, S) + (j & nbm);
@@ -306,7 +394,7 @@ __device__ __forceinline__ void prime_fold(float2* buf, int n, int S, int lgnb, 
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (e0 + u * NT < total) {
+            if (e0 + u * nt < total) {
                 const float2 ya = cmul(buf[ia[u]], wa[u]), yc = cmul(buf[ic[u]], wc[u]);
                 buf[ia[u]] = cadd(ya, yc);
                 buf[ic[u]] = csub(ya, yc);
@@ -343,25 +431,28 @@ __device__ __forceinline__ int root_step(int S, int lgnb) { return lgnb ? S : 1;
 // zero; rows q > h and columns r > h read it. Each wave takes result tiles
 // (column block, row block) round-robin and keeps at most kMfmaTilesPerWave of
 // them until every wave has read its inputs; the caller guarantees
-// mfma_tiles(totb, R) <= kMfmaTilesPerWave * NT / 64.
-template <int NT>
-__device__ __forceinline__ void stage_prime_mfma(float2* buf, int n, int S, int lgnb, int Ns, int R, float rns,
-                                                 float rh, const float2* __restrict__ tws,
-                                                 const float2* __restrict__ roots) {
-    constexpr int NW = NT / 64;
+// mfma_tiles(totb, R) <= kMfmaTilesPerWave * nt / 64.
+template <class NT>
+__device__ __forceinline__ void stage_prime_mfma(float2* buf, NT nt, const StageRec& st, int n, int S, int lgnb,
+                                                 const float2* __restrict__ tws,
+                                                 const float2* __restrict__ roots, const FftStage* next,
+                                                 RawRec& nraw) {
+    const int NW = nt >> 6;
+    const int R = st.R, Ns = st.Ns, m = st.m;
     constexpr int TPW = kMfmaTilesPerWave;
-    prime_fold<NT>(buf, n, S, lgnb, Ns, R, rns, rh, tws);
     const int tid = stage_tid();
     const int ts = root_step(S, lgnb);
     float2* tab = buf + root_slot0(n, S, lgnb);
-    {
-        const int stride = n / R;
-        for (int j = tid; j <= R; j += NT)
-            tab[__mul24(j, ts)] = j < R ? at32(roots, static_cast<uint32_t>(__mul24(j, stride))) : make_float2(0.f, 0.f);
-    }
+    // the first nt table entries are read before the fold and land during it
+    auto root = [&](int j) {
+        return j < R ? at32(roots, static_cast<uint32_t>(__mul24(j, m))) : make_float2(0.f, 0.f);
+    };
+    const float2 root0 = root(tid);
+    prime_fold(buf, nt, st, S, lgnb, tws);
+    if (tid <= R) tab[__mul24(tid, ts)] = root0;
+    for (int j = tid + nt; j <= R; j += nt) tab[__mul24(j, ts)] = root(j);
     __syncthreads();
-    const int lane = tid & 63, wave = tid >> 6;
-    const int m = n / R;
+    const int lane = tid & 63, wave = uni(tid >> 6);
     const int h = (R - 1) >> 1;
     const int nbm = (1 << lgnb) - 1;
     const int mS = __mul24(m, S), NsS = __mul24(Ns, S);
@@ -444,7 +535,8 @@ __device__ __forceinline__ void stage_prime_mfma(float2* buf, int n, int S, int 
         }
     }
     __syncthreads();
-    const Div dns = mkdiv(Ns, rns);
+    nraw = rec_fetch(next);
+    const Div dns = mkdiv(Ns, st.rns);
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
         const int tile = wave + i * NW;
@@ -474,51 +566,46 @@ __device__ __forceinline__ void stage_prime_mfma(float2* buf, int n, int S, int 
 }
 
 // Forward DFTs of nb = 2^lgnb sequences of length d->n, element i of
-// sequence t at buf[i S + t]. The stage twiddles and prime-radix matrices are
+// sequence t at buf[i S + t]. The stage twiddles and prime-radix roots are
 // read from the pool (each butterfly reads R - 1 consecutive twiddles, shared
 // by every workgroup of the same length, so they stay in the caches). The
 // plan guarantees that every prime-radix stage's result tiles fit the
 // workgroup. Ends with a barrier when there is a stage.
 // `stw` points at this length's stage twiddles: pool + d->stw, or a copy
-// of them (d->ntw values) in LDS.
-template <int NT, int EPT>
-__device__ __forceinline__ void lds_fft(float2* buf, int S, int lgnb, const FftDesc* __restrict__ d,
-                                        const float2* __restrict__ pool, const float2* __restrict__ stw) {
-    const int n = d->n;
-    const int ns = d->nstages;
-    int Ns = 1;
+// of them (d->ntw values) in LDS. PRE: see stage_fixed (first stage; the
+// transform's radices are compile-time ones then).
+template <int EPT, bool PRE, class NT, class Desc>
+__device__ __forceinline__ void lds_fft(float2* buf, NT nt, int S, int lgnb, const Desc* __restrict__ d,
+                                        const float2* __restrict__ pool, const float2* __restrict__ stw,
+                                        const float2* __restrict__ pre) {
+    const int ns = uni(d->nstages), n = uni(d->n);
+    RawRec raw = rec_fetch(d->st);
     for (int s = 0; s < ns; ++s) {
-        const int R = d->radix[s];
-        const float rns = d->rcp_ns[s];
-        const float2* tw = stw + d->stoff[s];
-        switch (R) {
-            case 2: stage_fixed<2, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 3: stage_fixed<3, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 4: stage_fixed<4, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 5: stage_fixed<5, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 6: stage_fixed<6, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 7: stage_fixed<7, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 8: stage_fixed<8, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 9: stage_fixed<9, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 10: stage_fixed<10, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 11: stage_fixed<11, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 12: stage_fixed<12, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 13: stage_fixed<13, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 14: stage_fixed<14, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 15: stage_fixed<15, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
-            case 16: stage_fixed<16, NT, EPT>(buf, n, S, lgnb, Ns, rns, tw); break;
+        const StageRec rec = rec_uniform(raw);
+        const FftStage* next = d->st + min(s + 1, ns - 1);
+        const float2* tw = stw + rec.stoff;
+        switch (rec.R) {
+            case 2: stage_fixed<2, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 3: stage_fixed<3, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 4: stage_fixed<4, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 5: stage_fixed<5, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 6: stage_fixed<6, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 7: stage_fixed<7, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 8: stage_fixed<8, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 9: stage_fixed<9, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 10: stage_fixed<10, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 11: stage_fixed<11, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 12: stage_fixed<12, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 13: stage_fixed<13, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 14: stage_fixed<14, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 15: stage_fixed<15, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
+            case 16: stage_fixed<16, EPT, PRE>(buf, nt, rec, S, lgnb, tw, pre, next, raw); break;
             default:
-                stage_prime_mfma<NT>(buf, n, S, lgnb, Ns, R, rns, d->rcp_h[s], tw, pool + d->full);
+                stage_prime_mfma(buf, nt, rec, n, S, lgnb, tw, pool + d->full, next, raw);
                 break;
         }
-        Ns *= R;
+        if (PRE) pre = nullptr;
     }
-}
-
-template <int NT, int EPT>
-__device__ __forceinline__ void lds_fft(float2* buf, int S, int lgnb, const FftDesc* __restrict__ d,
-                                        const float2* __restrict__ pool) {
-    lds_fft<NT, EPT>(buf, S, lgnb, d, pool, pool + d->stw);
 }
 
 // Interleave stride of nb = 2^lgnb sequences.

@@ -150,13 +150,13 @@ template <int NT, int EPT, bool SLICED>
 __global__ __launch_bounds__(NT) NSG_OCC void k_fwd_a(const float* __restrict__ x, float2* __restrict__ Y,
                                                       Pass p, Tables T, SliceIn sl, int batch, long long sig_stride) {
     extern __shared__ float2 lds[];
-    __shared__ FftDesc fdl;
+    __shared__ LdsDesc fdl;
     const FftDesc* fd = T.ffts + p.fft;
     float2 *t4, *buf;
     pass_lds(lds, p, true, t4, buf);
     float2* twl = buf;
     buf += p.ntw;
-    for (int i = threadIdx.x; i < static_cast<int>(sizeof(FftDesc) / 4); i += NT)
+    for (int i = threadIdx.x; i < kDescWords; i += NT)
         reinterpret_cast<int*>(&fdl)[i] = reinterpret_cast<const int*>(fd)[i];
     for (int i = threadIdx.x; i < p.ntw; i += NT) twl[i] = T.tw[fd->stw + i];
     load_tw4<NT>(t4, p, T);
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_fwd_a(const float* __restrict__ 
         }
         __syncthreads();
         if (t + static_cast<int>(gridDim.x) < G) fetch(t + gridDim.x);
-        lds_fft<NT, EPT>(buf, S, p.lgnb, &fdl, T.tw, twl);
+        lds_fft<EPT, false>(buf, FixedNt<NT>{}, S, p.lgnb, &fdl, T.tw, twl, nullptr);
         float2* Ys = Y + (long long)sig * p.L;
         for (int e = threadIdx.x; e < tot; e += NT) {
             const int c = e & nbm, k1 = e >> p.lgnb;
@@ -243,7 +243,7 @@ __device__ __forceinline__ float2 gather_bin(const float2* __restrict__ Ws, int 
     const float2 a = at32(Ws, i0), b = at32(Ws, i1), c = at32(Ws, i2);
     // masks instead of branches, so the compiler cannot sink the reads
     const float mb = cnt > 1 ? 1.f : 0.f, mc = cnt > 2 ? 1.f : 0.f;
-    return make_float2(a.x + mb * b.x + mc * c.x, a.y + mb * b.y + mc * c.y);
+    return make_float2(fmaf(mc, c.x, fmaf(mb, b.x, a.x)), fmaf(mc, c.y, fmaf(mb, b.y, a.y)));
 }
 
 // The same sum from a wide half-record: `head` as above, i1 and i2 the
@@ -252,7 +252,7 @@ __device__ __forceinline__ float2 gather_bin_abs(const float2* __restrict__ Ws, 
     const int i0 = head & ((1 << 29) - 1), cnt = static_cast<int>(static_cast<unsigned>(head) >> 29);
     const float2 a = at32(Ws, i0), b = at32(Ws, i1), c = at32(Ws, i2);
     const float mb = cnt > 1 ? 1.f : 0.f, mc = cnt > 2 ? 1.f : 0.f;
-    return make_float2(a.x + mb * b.x + mc * c.x, a.y + mb * b.y + mc * c.y);
+    return make_float2(fmaf(mc, c.x, fmaf(mb, b.x, a.x)), fmaf(mc, c.y, fmaf(mb, b.y, a.y)));
 }
 
 // ------------------------------- inverse packed FFT, pass A, with overlap-add
@@ -342,7 +342,8 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_inv_a(const float2* __restrict__
     }
     tw4_store<NT>(t4, t4pre, p, T);
     __syncthreads();
-    lds_fft<NT, EPT>(buf, S, p.lgnb, T.ffts + p.fft, T.tw);
+    const FftDesc* fd = T.ffts + p.fft;
+    lds_fft<EPT, false>(buf, FixedNt<NT>{}, S, p.lgnb, fd, T.tw, T.tw + fd->stw, nullptr);
     __syncthreads();
     float2* Ys = Y + (long long)sig * p.L;
     // output column of a slot (primary or mirror), -1 for an unused slot
@@ -374,11 +375,11 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_pass_b(const float2* __restrict_
     extern __shared__ float2 lds[];
     // the descriptor and stage twiddles are read from LDS inside the loop:
     // any global read there would have to wait for the prefetched rows first
-    __shared__ FftDesc fdl;
+    __shared__ LdsDesc fdl;
     const FftDesc* fd = T.ffts + p.fft;
     float2* twl = lds;
     float2* buf = lds + p.ntw;
-    for (int i = threadIdx.x; i < static_cast<int>(sizeof(FftDesc) / 4); i += NT)
+    for (int i = threadIdx.x; i < kDescWords; i += NT)
         reinterpret_cast<int*>(&fdl)[i] = reinterpret_cast<const int*>(fd)[i];
     for (int i = threadIdx.x; i < p.ntw; i += NT) twl[i] = T.tw[fd->stw + i];
     const int G = p.ntile * batch;
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_pass_b(const float2* __restrict_
         }
         __syncthreads();
         if (t + static_cast<int>(gridDim.x) < G) fetch(t + gridDim.x);
-        lds_fft<NT, EPT>(buf, S, p.lgnb, &fdl, T.tw, twl);
+        lds_fft<EPT, false>(buf, FixedNt<NT>{}, S, p.lgnb, &fdl, T.tw, twl, nullptr);
         float2* os = out + (long long)sig * out_stride;
         for (int e = threadIdx.x; e < tot; e += NT) {
             const int r = e & nbm, k2 = e >> p.lgnb;
@@ -426,13 +427,13 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_pass_b(const float2* __restrict_
 }
 
 // ------------------------------------------------------------ band analysis
-// Entries of nb = 2^lg interleaved sequences of length n: thread tid owns
-// sequence tid & (nb - 1) and its entries i = (tid >> lg) + j (NT >> lg) < n,
+// Entries of nb = 2^lg interleaved sequences of length n: thread tid < nt owns
+// sequence tid & (nb - 1) and its entries i = (tid >> lg) + j (nt >> lg) < n,
 // U at a time; as in load_phase, all U gets are issued before the first put,
 // and get only sees valid indices.
-template <int NT, int U, class Get, class Put>
-__device__ __forceinline__ void seq_phase(int n, int lg, Get get, Put put) {
-    const int step = NT >> lg;
+template <int U, class NT, class Get, class Put>
+__device__ __forceinline__ void seq_phase(NT nt, int n, int lg, Get get, Put put) {
+    const int step = nt >> lg;
     using V = decltype(get(0));
     for (int i0 = static_cast<int>(threadIdx.x) >> lg; i0 < n; i0 += U * step) {
         V v[U];
@@ -468,40 +469,26 @@ __device__ __forceinline__ float2 route_value(float4 r, float2 za, float2 zb) {
 }
 
 // The transform descriptor of a band work item, copied to LDS in two steps:
-// desc_fetch issues its global reads into registers, desc_store writes them
-// to LDS. Between the two the kernel issues its router or coefficient reads,
-// so the descriptor's round trip overlaps theirs instead of preceding them.
-template <int NT>
+// fetch issues its global reads into registers, store writes them to LDS.
+// Between the two the kernel issues its router or coefficient reads, so the
+// descriptor's round trip overlaps theirs instead of preceding them.
 struct DescCopy {
-    static constexpr int kWords = static_cast<int>(sizeof(FftDesc) / 4);
-    static constexpr int kPer = (kWords + NT - 1) / NT;
+    static constexpr int kPer = (kDescWords + 63) / 64;   // for the smallest workgroup, one wave
     int w[kPer];
-    __device__ __forceinline__ void fetch(const FftDesc* d) {
+    __device__ __forceinline__ void fetch(const FftDesc* d, int nt) {
         const int* src = reinterpret_cast<const int*>(d);
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) w[u] = src[min(static_cast<int>(threadIdx.x) + u * NT, kWords - 1)];
+        for (int u = 0; u < kPer; ++u) w[u] = src[min(static_cast<int>(threadIdx.x) + u * nt, kDescWords - 1)];
     }
-    __device__ __forceinline__ void store(FftDesc* l) const {
+    __device__ __forceinline__ void store(LdsDesc* l, int nt) const {
         int* dst = reinterpret_cast<int*>(l);
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
-            const int i = static_cast<int>(threadIdx.x) + u * NT;
-            if (i < kWords) dst[i] = w[u];
+            const int i = static_cast<int>(threadIdx.x) + u * nt;
+            if (i < kDescWords) dst[i] = w[u];
         }
     }
 };
-
-// Bluestein's middle step on the LDS sequences: v <- conj(v K) for the
-// transformed kernel K (entries 0 .. n-1), sequence sg of this thread.
-template <int NT>
-__device__ __forceinline__ void blu_middle(float2* buf, int n, int lg, int S, int sg, const float2* K) {
-    seq_phase<NT, 4>(
-        n, lg, [&](int i) { return at32(K, i); },
-        [&](int i, float2 kv) {
-            const int a = __mul24(i, S) + sg;
-            buf[a] = conjf2(cmul(buf[a], kv));
-        });
-}
 
 // One workgroup per work item (band, signals s0 .. s0 + count - 1, interleaved
 // as 2^lgnb sequences). For entry i < W of the band (bin k = k_lo + i; slots
@@ -513,20 +500,18 @@ __device__ __forceinline__ void blu_middle(float2* buf, int n, int lg, int S, in
 // above kMfmaMaxRadix (or for which it is cheaper) use Bluestein's algorithm: with ch_m = exp(-i pi m^2/M),
 // F_M v = ch * conj(F_P conj(F_P(ch v) * K)) where K = F_P(b)/P and b the
 // cyclic chirp exp(+i pi t^2/M), |t| < M.
-template <int NT, int EPT>
-__global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2* __restrict__ Z, float2* __restrict__ coef,
-                                                              const float4* __restrict__ rt, Tables T, int item0,
-                                                              int nitems, int batch, int L, long long C) {
-    extern __shared__ float2 lds[];
-    const WorkItem it = T.items[item0 + blockIdx.x];
+template <int EPT, class NT>
+__device__ __forceinline__ void band_analysis(NT nt, const WorkItem& it, float2* lds, const float2* __restrict__ Z,
+                                              float2* __restrict__ coef, const float4* __restrict__ rt,
+                                              const Tables& T, int batch, int L, long long C) {
     const int g = min(it.count, batch - it.s0);
     if (g <= 0) return;
     const BandDev& bd = it.bd;
     // the descriptor goes to LDS (the stage loop then issues no global
     // descriptor reads); its read overlaps the router's
-    __shared__ FftDesc fdl;
-    DescCopy<NT> dsc;
-    dsc.fetch(T.ffts + bd.fft);
+    __shared__ LdsDesc fdl;
+    DescCopy dsc;
+    dsc.fetch(T.ffts + bd.fft, nt);
     float2* buf = lds;
     const int M = bd.M, n = bd.n;
     const int lg = it.lgnb, nb = 1 << lg, S = seq_stride(lg);
@@ -544,8 +529,7 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2*
     struct RouteIn { float2 za, zb, ch; float4 r; };
     auto route = [&](auto blu_t) {
         constexpr bool BLU = decltype(blu_t)::value;
-        seq_phase<NT, 4>(
-            M, lg,
+        seq_phase<4>(nt, M, lg,
             [&](int i) {
                 int slot = i + bd.rot;
                 if (slot >= M) slot -= M;
@@ -577,7 +561,7 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2*
     auto route_fast = [&](auto blu_t) {
         constexpr bool BLU = decltype(blu_t)::value;
         constexpr int RP = 2;                     // pairs per batch
-        const int st = NT >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
+        const int st = nt >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
         const int wl = live ? bd.W : 0;
         const int st2 = 2 * st;
         int slot = 2 * p0 + bd.rot;               // < 2 M whenever 2 p0 < M
@@ -630,24 +614,22 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2*
         if (blu) route(std::true_type{});
         else route(std::false_type{});
     }
-    dsc.store(&fdl);
+    dsc.store(&fdl, nt);
     if (blu)
-        for (int e = threadIdx.x; e < ((n - M) << lg); e += NT)
+        for (int e = threadIdx.x; e < ((n - M) << lg); e += nt)
             buf[__mul24(M + (e >> lg), S) + (e & (nb - 1))] = make_float2(0.f, 0.f);
     __syncthreads();
-    lds_fft<NT, EPT>(buf, S, lg, &fdl, T.tw);
-    if (blu) {
-        blu_middle<NT>(buf, n, lg, S, sg, T.kern + bd.kern);
-        __syncthreads();
-        lds_fft<NT, EPT>(buf, S, lg, &fdl, T.tw);
+    // Bluestein: a second transform, whose first stage reads conj(v K)
+    for (int rep = 0;; ++rep) {
+        lds_fft<EPT, true>(buf, nt, S, lg, &fdl, T.tw, T.tw + uni(fdl.stw), rep ? T.kern + bd.kern : nullptr);
+        if (!blu || rep) break;
     }
     if (!live) return;
     float2* cb = coef + (long long)it.s0 * C + bd.off;
     const uint32_t crow = static_cast<uint32_t>(sg) * static_cast<uint32_t>(C);
     // mixed radix: c = conj(V) / M; Bluestein: c = conj(ch * conj(D)) / M = conj(ch) D / M
     if (blu) {
-        seq_phase<NT, 4>(
-            M, lg, [&](int i) { return at32(chb, i); },
+        seq_phase<4>(nt, M, lg, [&](int i) { return at32(chb, i); },
             [&](int i, float2 chi) {
                 at32(cb, crow + i) = cscale(cmul(conjf2(chi), buf[__mul24(i, S) + sg]), bd.inv_M);
             });
@@ -655,7 +637,7 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2*
         // pairs of entries (i, i + 1), i = 2 (p0 + j st), two at a time: one
         // 16-byte write per pair at addresses affine in j (scalar base, one
         // lane offset); a lone last entry is written on its own
-        const int st = NT >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
+        const int st = nt >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
         const int st2 = 2 * st, stS = __mul24(st2, S);
         int a = __mul24(2 * p0, S) + sg;
         for (int ib = 2 * p0; ib < M; ib += 2 * st2) {
@@ -676,23 +658,30 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2*
     }
 }
 
+template <int NT, int EPT>
+__global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2* __restrict__ Z, float2* __restrict__ coef,
+                                                              const float4* __restrict__ rt, Tables T, int item0,
+                                                              int nitems, int batch, int L, long long C) {
+    extern __shared__ float2 lds[];
+    const WorkItem it = T.items[item0 + blockIdx.x];
+    band_analysis<EPT>(FixedNt<NT>{}, it, lds, Z, coef, rt, T, batch, L, C);
+}
+
 // ----------------------------------------------------------- band synthesis
 // One workgroup per work item: U = F_M c (eq. 10), then the weighted band
 // spectrum W[off + i] = w_i U[slot(k_lo + i)] in bin order for the support
 // entries i < W (w = h for S, the T^dagger weight for T^dagger). Overlapping bands are summed later by the
 // owner of each bin.
-template <int NT, int EPT>
-__global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2* __restrict__ coef, float2* __restrict__ W,
-                                                               const float* __restrict__ wt, Tables T, int item0,
-                                                               int nitems, int batch, long long C) {
-    extern __shared__ float2 lds[];
-    const WorkItem it = T.items[item0 + blockIdx.x];
+template <int EPT, class NT>
+__device__ __forceinline__ void band_synthesis(NT nt, const WorkItem& it, float2* lds, const float2* __restrict__ coef,
+                                               float2* __restrict__ W, const float* __restrict__ wt,
+                                               const Tables& T, int batch, long long C) {
     const int g = min(it.count, batch - it.s0);
     if (g <= 0) return;
     const BandDev& bd = it.bd;
-    __shared__ FftDesc fdl;
-    DescCopy<NT> dsc;
-    dsc.fetch(T.ffts + bd.fft);
+    __shared__ LdsDesc fdl;
+    DescCopy dsc;
+    dsc.fetch(T.ffts + bd.fft, nt);
     float2* buf = lds;
     const int M = bd.M, n = bd.n;
     const int lg = it.lgnb, nb = 1 << lg, S = seq_stride(lg);
@@ -707,7 +696,7 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2
     // of the coefficients each (and of the chirp for Bluestein)
     auto load_fast = [&](auto blu_t) {
         constexpr bool BLU = decltype(blu_t)::value;
-        const int st = NT >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
+        const int st = nt >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
         const int st2 = 2 * st, stS = __mul24(st2, S);
         int a = __mul24(2 * p0, S) + sg;
         for (int ib = 2 * p0; ib < M; ib += 2 * st2) {
@@ -736,27 +725,24 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2
         if (blu) load_fast(std::true_type{});
         else load_fast(std::false_type{});
     } else if (blu) {
-        seq_phase<NT, 4>(
-            M, lg, [&](int i) { return make_float4_2(at32(cb, crow + i), at32(chb, i)); },
+        seq_phase<4>(nt, M, lg, [&](int i) { return make_float4_2(at32(cb, crow + i), at32(chb, i)); },
             [&](int i, float4 r) {
                 buf[__mul24(i, S) + sg] = live ? cmul(make_float2(r.x, r.y), make_float2(r.z, r.w))
                                                : make_float2(0.f, 0.f);
             });
     } else {
-        seq_phase<NT, 4>(
-            M, lg, [&](int i) { return at32(cb, crow + i); },
+        seq_phase<4>(nt, M, lg, [&](int i) { return at32(cb, crow + i); },
             [&](int i, float2 v) { buf[__mul24(i, S) + sg] = live ? v : make_float2(0.f, 0.f); });
     }
-    dsc.store(&fdl);
+    dsc.store(&fdl, nt);
     if (blu)
-        for (int e = threadIdx.x; e < ((n - M) << lg); e += NT)
+        for (int e = threadIdx.x; e < ((n - M) << lg); e += nt)
             buf[__mul24(M + (e >> lg), S) + (e & (nb - 1))] = make_float2(0.f, 0.f);
     __syncthreads();
-    lds_fft<NT, EPT>(buf, S, lg, &fdl, T.tw);
-    if (blu) {
-        blu_middle<NT>(buf, n, lg, S, sg, T.kern + bd.kern);
-        __syncthreads();
-        lds_fft<NT, EPT>(buf, S, lg, &fdl, T.tw);
+    // Bluestein: a second transform, whose first stage reads conj(v K)
+    for (int rep = 0;; ++rep) {
+        lds_fft<EPT, true>(buf, nt, S, lg, &fdl, T.tw, T.tw + uni(fdl.stw), rep ? T.kern + bd.kern : nullptr);
+        if (!blu || rep) break;
     }
     if (!live) return;
     const float* w = wt + bd.off;
@@ -764,8 +750,7 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2
     struct OutIn { float2 ch; float w; };
     auto weigh = [&](auto blu_t) {
         constexpr bool BLU = decltype(blu_t)::value;
-        seq_phase<NT, 4>(
-            bd.W, lg,
+        seq_phase<4>(nt, bd.W, lg,
             [&](int i) {
                 int slot = i + bd.rot;
                 if (slot >= M) slot -= M;
@@ -784,7 +769,7 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2
     // guard covers the reads past the support)
     auto weigh_fast = [&](auto blu_t) {
         constexpr bool BLU = decltype(blu_t)::value;
-        const int st = NT >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
+        const int st = nt >> lg, p0 = static_cast<int>(threadIdx.x) >> lg;
         const int st2 = 2 * st, Wd = bd.W;
         int slot = 2 * p0 + bd.rot;               // < 2 M whenever 2 p0 < W
         slot = slot >= M ? slot - M : slot;
@@ -820,6 +805,15 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2
     };
     if (blu) weigh_fast(std::true_type{});
     else weigh_fast(std::false_type{});
+}
+
+template <int NT, int EPT>
+__global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2* __restrict__ coef, float2* __restrict__ W,
+                                                              const float* __restrict__ wt, Tables T, int item0,
+                                                              int nitems, int batch, long long C) {
+    extern __shared__ float2 lds[];
+    const WorkItem it = T.items[item0 + blockIdx.x];
+    band_synthesis<EPT>(FixedNt<NT>{}, it, lds, coef, W, wt, T, batch, C);
 }
 
 // ------------------------------------------------------------ huge bands
@@ -898,7 +892,7 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_big_a(BigArgs a, Tables T, int i
         buf[__mul24(r, S) + c] = v;
     }
     __syncthreads();
-    lds_fft<NT, EPT>(buf, S, lg, fd1, T.tw);
+    lds_fft<EPT, false>(buf, FixedNt<NT>{}, S, lg, fd1, T.tw, T.tw + fd1->stw, nullptr);
     __syncthreads();
     float2* Y = a.H1 + hbase;
     for (int e = threadIdx.x; e < tot; e += NT) {
@@ -936,7 +930,7 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_big_b(BigArgs a, Tables T, int i
         buf[__mul24(c, S) + r] = r < rows ? Y[e] : make_float2(0.f, 0.f);
     }
     __syncthreads();
-    lds_fft<NT, EPT>(buf, S, lg, fd2, T.tw);
+    lds_fft<EPT, false>(buf, FixedNt<NT>{}, S, lg, fd2, T.tw, T.tw + fd2->stw, nullptr);
     const bool to_mid = blu && !second;
     for (int e = threadIdx.x; e < tot; e += NT) {
         const int r = e & nbm, k2 = e >> lg;

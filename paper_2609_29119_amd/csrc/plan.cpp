@@ -135,7 +135,6 @@ struct FftRegistry {
         FftDesc d{};
         d.n = static_cast<int32_t>(n);
         d.nstages = static_cast<int32_t>(rad.size());
-        for (size_t s = 0; s < rad.size(); ++s) d.radix[s] = static_cast<int16_t>(rad[s]);
         d.full = static_cast<int32_t>(p.twpool.size() / 2);
         for (int64_t t = 0; t < n; ++t) push_c(p.twpool, root(t, n));
         int lg = 0;
@@ -149,9 +148,13 @@ struct FftRegistry {
         int64_t Ns = 1, off = 0;
         for (size_t s = 0; s < rad.size(); ++s) {
             const int64_t R = rad[s];
-            d.rcp_ns[s] = static_cast<float>(1.0 / static_cast<double>(Ns));
-            d.rcp_h[s] = R > 16 ? static_cast<float>(1.0 / static_cast<double>((R - 1) / 2)) : 0.0f;
-            d.stoff[s] = static_cast<int32_t>(off);
+            FftStage& st = d.st[s];
+            st.R = static_cast<int32_t>(R);
+            st.Ns = static_cast<int32_t>(Ns);
+            st.m = static_cast<int32_t>(n / R);
+            st.rcp_ns = static_cast<float>(1.0 / static_cast<double>(Ns));
+            st.rcp_h = R > 16 ? static_cast<float>(1.0 / static_cast<double>((R - 1) / 2)) : 0.0f;
+            st.stoff = static_cast<int32_t>(off);
             if (s > 0) {
                 const int64_t stride = n / (Ns * R);
                 for (int64_t k = 0; k < Ns; ++k)

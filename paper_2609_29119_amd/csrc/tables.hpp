@@ -22,12 +22,28 @@ constexpr int kMfmaTilesPerWave = 4;
 // columns: blocks of 8 complex columns times blocks of 16 outputs q = 0..(R-1)/2.
 inline constexpr int mfma_tiles(int totb, int R) { return ((totb + 7) >> 3) * (((R - 1) / 2 + 16) >> 4); }
 
+// One Stockham stage of a transform: radix R over Ns = product of the earlier
+// radices, m = n / R butterflies, its twiddles at stw + stoff. Everything a
+// stage needs that does not depend on the data is worked out by the plan, so
+// a stage starts from one 32-byte record instead of integer divisions.
+struct FftStage {
+    int32_t R;
+    int32_t Ns;
+    int32_t m;
+    int32_t stoff;
+    // 1 / Ns and, for a prime radix R > 16, 1 / ((R - 1) / 2), rounded once to
+    // fp32; the stage's quotient-and-remainder steps start from these (see Div)
+    float rcp_ns;
+    float rcp_h;
+    int32_t pad[2];
+};
+
 // One transform length n: Stockham stages of the given radices, applied in
 // order. Twiddle pool layout per length: the full table omega_n^t (t < n) at
 // `full`, the two-level table (hi: nhi values, lo: 2^lg values) right after
 // it, and the stage twiddles at `stw`: for stage s >= 1 with radix R over
 // Ns = product of the earlier radices, omega_{Ns R}^{r k} at
-// stw + stoff[s] + k (R - 1) + r - 1 for k < Ns, 1 <= r < R (ntw values in all).
+// stw + st[s].stoff + k (R - 1) + r - 1 for k < Ns, 1 <= r < R (ntw values in all).
 struct FftDesc {
     int32_t n;
     int32_t nstages;
@@ -36,14 +52,22 @@ struct FftDesc {
     int32_t nhi;
     int32_t stw;
     int32_t ntw;
-    int16_t radix[kMaxStages];
-    int32_t stoff[kMaxStages];
-    // per stage: 1 / Ns (the product of the earlier radices) and, for a prime
-    // radix R > 16, 1 / ((R - 1) / 2), rounded once to fp32; the stages'
-    // quotient-and-remainder steps start from these (see Div)
-    float rcp_ns[kMaxStages];
-    float rcp_h[kMaxStages];
+    int32_t pad;
+    FftStage st[kMaxStages];
 };
+
+// Words of a descriptor that the kernels copy to LDS: the header and the
+// first kLdsStages stages. Lengths up to kMaxLdsFft, the longest a workgroup
+// transforms, have at most six stages (5^6 = 15625: two factors 5 do not fit
+// one radix).
+constexpr int kMaxLdsFft = 16384;
+constexpr int kLdsStages = 8;
+constexpr int kDescWords = static_cast<int>(sizeof(FftDesc) / 4 - (kMaxStages - kLdsStages) * sizeof(FftStage) / 4);
+struct LdsDesc {
+    int32_t n, nstages, full, lg, nhi, stw, ntw, pad;
+    FftStage st[kLdsStages];
+};
+static_assert(sizeof(LdsDesc) == 4 * kDescWords, "LdsDesc is a prefix of FftDesc");
 
 // One band of the layout as the band kernels see it.
 struct BandDev {
