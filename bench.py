@@ -257,8 +257,8 @@ def stage_of_kernel(name):
     import re
     if re.search(r"\bk_ola\b", name):
         return "sliced_overlap_add"
-    m = re.search(r"k_(fwd_a|inv_a|pass_b|band_analysis|band_synthesis|big_a|big_b)<(\d+), (\d+)(?:, (true|false))?>",
-                  name)
+    m = re.search(r"k_(fwd_a|inv_a|pass_b|band_analysis(?:_all)?|band_synthesis(?:_all)?|big_a|big_b)"
+                  r"<(\d+), (\d+)(?:, (true|false))?>", name)
     if not m:
         return None
     k, nt, ept, inv = m.groups()
@@ -271,6 +271,8 @@ def stage_of_kernel(name):
     if k in ("big_a", "big_b"):
         # one kernel per pass serves both directions
         return "huge_band_" + ("columns" if k == "big_a" else "rows")
+    if k.endswith("_all"):
+        return k
     return f"{k}_{nt}x{ept}"
 
 

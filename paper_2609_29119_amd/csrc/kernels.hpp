@@ -667,6 +667,18 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_analysis(const float2*
     band_analysis<EPT>(FixedNt<NT>{}, it, lds, Z, coef, rt, T, batch, L, C);
 }
 
+// All bands of a plan in one launch (see the plan's rule): a workgroup has the
+// threads of the largest item, the waves an item does not use end at once.
+template <int NT, int EPT>
+__global__ __launch_bounds__(NT) NSG_OCC void k_band_analysis_all(const float2* __restrict__ Z, float2* __restrict__ coef,
+                                                              const float4* __restrict__ rt, Tables T, int item0,
+                                                              int nitems, int batch, int L, long long C) {
+    extern __shared__ float2 lds[];
+    const WorkItem it = T.items[item0 + blockIdx.x];
+    if (static_cast<int>(threadIdx.x) >= it.nt) return;
+    band_analysis<EPT>(ItemNt{it.nt}, it, lds, Z, coef, rt, T, batch, L, C);
+}
+
 // ----------------------------------------------------------- band synthesis
 // One workgroup per work item: U = F_M c (eq. 10), then the weighted band
 // spectrum W[off + i] = w_i U[slot(k_lo + i)] in bin order for the support
@@ -814,6 +826,16 @@ __global__ __launch_bounds__(NT) NSG_OCC_BAND void k_band_synthesis(const float2
     extern __shared__ float2 lds[];
     const WorkItem it = T.items[item0 + blockIdx.x];
     band_synthesis<EPT>(FixedNt<NT>{}, it, lds, coef, W, wt, T, batch, C);
+}
+
+template <int NT, int EPT>
+__global__ __launch_bounds__(NT) NSG_OCC void k_band_synthesis_all(const float2* __restrict__ coef, float2* __restrict__ W,
+                                                              const float* __restrict__ wt, Tables T, int item0,
+                                                              int nitems, int batch, long long C) {
+    extern __shared__ float2 lds[];
+    const WorkItem it = T.items[item0 + blockIdx.x];
+    if (static_cast<int>(threadIdx.x) >= it.nt) return;
+    band_synthesis<EPT>(ItemNt{it.nt}, it, lds, coef, W, wt, T, batch, C);
 }
 
 // ------------------------------------------------------------ huge bands

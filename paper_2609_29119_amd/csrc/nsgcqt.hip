@@ -211,21 +211,14 @@ int upload(nsgcqt_plan_s* p) {
 
 // Launch schedule of the band phase, from the host plan alone. Overlap pays
 // when no band launch fills the GPU by itself and the band phase is long
-// against the fork and join (~25 us each way): at least 6M element slots of
-// band work. Then units are enqueued longest first, each onto the least
+// against the fork and join (~25 us each way): the plan's fan flag. Then units are enqueued longest first, each onto the least
 // loaded of the four streams; otherwise in bucket order on the caller's.
 void schedule(nsgcqt_plan_s* p) {
     const HostPlan& h = p->h;
     std::vector<double> cost;
-    int most = 0;
-    for (const auto& bk : h.buckets) {
-        most = std::max(most, bk.nitems);
-        cost.push_back(static_cast<double>(bk.nitems) * bk.nt * bk.ept);
-    }
+    for (const auto& bk : h.buckets) cost.push_back(bk.slots);
     if (!h.bigs.empty()) cost.push_back(4.0 * static_cast<double>(h.Hn) * static_cast<double>(h.batch));
-    double work = 0.0;
-    for (double c : cost) work += c;
-    p->fan = most < 2048 && work >= 6e6;
+    p->fan = h.fan && cost.size() > 1;
     p->order.resize(cost.size());
     for (size_t i = 0; i < cost.size(); ++i) p->order[i] = static_cast<int>(i);
     p->lane.assign(cost.size(), 0);
@@ -482,6 +475,12 @@ int run_bucket(nsgcqt_plan_s* p, size_t bi, bool analysis, const float2* in, flo
         ev_end(p, s);
         return NSGCQT_OK;
     };
+    if (bk.all) {
+        if (bk.ept == 16) return go(k_band_analysis_all<1024, 16>, k_band_synthesis_all<1024, 16>);
+        if (bk.nt == 256) return go(k_band_analysis_all<256, 8>, k_band_synthesis_all<256, 8>);
+        if (bk.nt == 512) return go(k_band_analysis_all<512, 8>, k_band_synthesis_all<512, 8>);
+        return go(k_band_analysis_all<1024, 8>, k_band_synthesis_all<1024, 8>);
+    }
     if (bk.nt == 64) return go(k_band_analysis<64, 8>, k_band_synthesis<64, 8>);
     if (bk.nt == 256 && bk.ept == 8) return go(k_band_analysis<256, 8>, k_band_synthesis<256, 8>);
     if (bk.nt == 256) return go(k_band_analysis<256, 16>, k_band_synthesis<256, 16>);
@@ -956,7 +955,7 @@ int nsgcqt_stage_info(nsgcqt_plan p, int op, int i, char* name, size_t cap, doub
         }
         const Bucket& bk = h.buckets[u];
         const double cb = static_cast<double>(bk.coeffs);
-        const std::string shape = std::to_string(bk.nt) + "x" + std::to_string(bk.ept);
+        const std::string shape = bk.all ? "all" : std::to_string(bk.nt) + "x" + std::to_string(bk.ept);
         if (an) st.push_back({"band_analysis_" + shape, (cb / C * 8.0 * L + 8.0 * cb) * b});
         else st.push_back({"band_synthesis_" + shape, 16.0 * cb * b});
     }

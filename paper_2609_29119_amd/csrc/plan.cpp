@@ -301,6 +301,83 @@ int64_t bluestein_length(int64_t M, int64_t row_bytes, double* cost) {
 
 namespace {
 
+// Element slots of a band phase from which it counts as long: shorter phases
+// run in one launch, longer ones in one launch per tier, on several streams
+// where no launch fills the GPU (below).
+constexpr double kLongPhase = 6e6;
+
+// A band's work item in the one-launch band phase: 2^lg interleaved signals in
+// nt threads (a multiple of 64) of at most `ept` elements each.
+struct OneFit {
+    int lg, nt;
+    double cost;   // estimated duration, SIMD cycles of one wave
+};
+
+// Up to 2048 elements per item: at 1024 and 512 the smaller items cost 2 to 8 %
+// more over 8 to 32 signals, 4096 and 8192 are equal. A matrix-core stage gets
+// a wave per result tile as far as the launch's block size goes (a plan whose
+// only large items are such stages would otherwise pay for it with residency);
+// its tiles run one after the other in a wave, which is what the longest small
+// bands wait for. Neither choice changes a result bit.
+OneFit one_fit(int n, int lg_cap, int ept, int block, int batch, int64_t row_bytes) {
+    std::vector<int> rad;
+    factor_radices(n, rad);
+    const int lg = std::min(lg_cap, seq_lg(n, 2048, batch, row_bytes));
+    int64_t nt = ((static_cast<int64_t>(n) << lg) + ept - 1) / ept;
+    for (int R : rad)
+        if (R > 16) {
+            const int64_t t = mfma_tiles(static_cast<int>((n / R) << lg), R);
+            nt = std::max<int64_t>(nt, 64 * ((t + kMfmaTilesPerWave - 1) / kMfmaTilesPerWave));
+            nt = std::max<int64_t>(nt, std::min<int64_t>(block, 64 * t));
+        }
+    nt = std::min<int64_t>(1024, std::max<int64_t>(64, (nt + 63) / 64 * 64));
+    return OneFit{lg, static_cast<int>(nt),
+                  stage_cost(rad, n, lg) * (1 << lg) * 64.0 / static_cast<double>(nt) + 2000.0 * rad.size()};
+}
+
+// How the band phase is launched, from the tiers of its bands (p.buckets) alone.
+// Sets p.fan and returns the largest transform length that goes into the one
+// launch, 0 for one launch per tier, -1 if a band does not fit its tier's LDS.
+//  - Short phases run in one launch. A launch of few workgroups lasts as long
+//    as its longest one (10 to 30 us) however few they are, and the tiers'
+//    launches of a call wait for each other: 3 x 50,274 samples at 24 bands
+//    per octave 105 -> 49 us a round trip, 1 x 220,500 221 -> 85 us, 32 x
+//    88,200 at 36 bands per octave (2.8M coefficients) 157 -> 135 us.
+//  - From kLongPhase on the launches fill the GPU or nearly do, and a launch
+//    whose workgroups all reserve the largest item's threads and LDS costs more
+//    than the waits: 64 x 88,200 215 us in one launch, 208 us by tier; 48 x
+//    177 and 183 us.
+//  - Long phases without a launch that fills the GPU fan out over streams
+//    (see the schedule). Beside a huge-band chain, which is the longest of
+//    their units, the tiers share one launch: two forks fewer (1 x 2,880,000
+//    365 -> 341 us, 6 x 500,000 285 -> 270 us). The 16,384-point tier joins
+//    it for up to two items per compute unit, since every workgroup then
+//    reserves 128 KB of LDS (1 x 2,000,000 284 -> 270 us; beyond, 3 x
+//    1,000,000 300 -> 309 us).
+//  - Plans of fewer than 32 bands keep their tiers: there is little to merge.
+int plan_launches(HostPlan& p, const std::vector<int>& work, const std::vector<BandFit>& fit, int64_t row_bytes) {
+    double slots = 4.0 * static_cast<double>(p.Hn) * static_cast<double>(p.batch);
+    int64_t items = 0, most = 0;
+    for (const auto& bk : p.buckets) {
+        int64_t here = 0;
+        for (int32_t l : bk.bands) {
+            const int lg = std::min(seq_lg(work[l], bk.nt * bk.ept, p.batch, row_bytes), fit[l].lg_cap);
+            here += (p.batch + (1 << lg) - 1) >> lg;
+            // what a tier's launch cannot hold is refused in either form
+            if (lds_slots(work[l], lg) * 8 > 160 * 1024) return -1;
+        }
+        slots += static_cast<double>(here) * bk.nt * bk.ept;
+        items += here;
+        most = std::max(most, here);
+    }
+    const bool is_long = slots >= kLongPhase;
+    p.fan = is_long && most < 2048;
+    if (p.bands.size() < 32) return 0;
+    if (!is_long) return 16384;
+    if (p.fan && !p.bigs.empty()) return items <= 512 ? 16384 : 8192;
+    return 0;
+}
+
 // Checks and settings shared by both plan builders.
 int begin_plan(HostPlan& p, double fs, int64_t N, int batch, bool sliced, std::string& err) {
     if (!(N >= 4) || (N % 2) != 0)
@@ -859,33 +936,75 @@ int finish_plan(HostPlan& p, std::string& err) {
     // one work item per (band, group of signals): small transforms of one band
     // for several signals share a workgroup, up to nt * ept elements
     p.items.clear();
+    auto add_items = [&](Bucket& bk, int32_t l, int lg, int nt) {
+        const int n = work[l], G = 1 << lg;
+        bk.lds_elems = std::max(bk.lds_elems, lds_slots(n, lg));
+        bk.slots += static_cast<double>((batch + G - 1) / G) * (bk.all ? static_cast<double>(n) * G : static_cast<double>(bk.nt) * bk.ept);
+        // fast load phases (WorkItem flags): every read up to entry
+        // M - 1 + 3 st of the band stays in the data or the guards
+        const auto& hb = p.bands[static_cast<size_t>(l)];
+        const int64_t st = nt >> lg, reach = hb.M - 1 + 3 * st;
+        int32_t fast = 0;
+        if (hb.k_lo >= 1 && hb.k_lo + hb.M <= L && hb.k_lo + reach < L + kFastGuard && 3 * st <= L &&
+            hb.off + reach < p.C + kFastGuard)
+            fast |= kItemFastRoute;
+        if (hb.off + reach < p.C) fast |= kItemFastCoef;
+        for (int s0 = 0; s0 < batch; s0 += G)
+            p.items.push_back(
+                WorkItem{l, s0, std::min(G, batch - s0), lg, fast, nt, p.banddev[static_cast<size_t>(l)]});
+    };
+    const int one_max = plan_launches(p, work, fit, row_bytes);
+    if (one_max < 0) return fail(err, NSGCQT_EUNSUPPORTED, "band kernel exceeds LDS");
+    if (one_max > 0) {
+        // one launch of 8 elements per thread (16 when it holds a band of more
+        // than 8192 points), longest items first
+        Bucket one{};
+        one.all = true;
+        one.ept = 8;
+        std::vector<int32_t> order;
+        std::vector<Bucket> rest;
+        for (auto& t : p.buckets) {
+            const int size = t.nt * t.ept;
+            if (size > one_max) {
+                rest.push_back(t);
+                continue;
+            }
+            order.insert(order.end(), t.bands.begin(), t.bands.end());
+            if (size > 8192) one.ept = 16;
+        }
+        std::vector<OneFit> of(p.bands.size());
+        for (int32_t l : order) {
+            const int nt = one_fit(work[l], fit[l].lg_cap, one.ept, 0, batch, row_bytes).nt;
+            one.nt = std::max(one.nt, nt <= 256 ? 256 : nt <= 512 ? 512 : 1024);
+        }
+        if (one.ept == 16) one.nt = 1024;
+        for (int32_t l : order) of[l] = one_fit(work[l], fit[l].lg_cap, one.ept, one.nt, batch, row_bytes);
+        std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+            auto c = [&](int32_t l) { return of[l].cost * (p.banddev[l].chirp >= 0 ? 2.0 : 1.0); };
+            return c(x) > c(y);
+        });
+        for (int32_t l : order) {
+            add_items(one, l, of[l].lg, of[l].nt);
+            one.bands.push_back(l);
+            one.max_work = std::max(one.max_work, work[l]);
+            one.coeffs += p.bands[l].M;
+        }
+        one.nitems = static_cast<int>(p.items.size());
+        p.buckets = std::move(rest);
+        if (one.nitems) p.buckets.insert(p.buckets.begin(), std::move(one));
+    }
     for (auto& bk : p.buckets) {
+        if (bk.all) continue;
         bk.item_off = static_cast<int>(p.items.size());
         const int E = bk.nt * bk.ept;
-        bk.lds_elems = 0;
-        for (int32_t l : bk.bands) {
-            const int n = work[l];
-            // 2^lg interleaved signals (seq_lg, within the band's matrix-tile cap)
-            const int lg = std::min(seq_lg(n, E, batch, row_bytes), fit[l].lg_cap);
-            const int G = 1 << lg;
-            bk.lds_elems = std::max(bk.lds_elems, lds_slots(n, lg));
-            // fast load phases (WorkItem flags): every read up to entry
-            // M - 1 + 3 st of the band stays in the data or the guards
-            const auto& hb = p.bands[static_cast<size_t>(l)];
-            const int64_t st = bk.nt >> lg, reach = hb.M - 1 + 3 * st;
-            int32_t fast = 0;
-            if (hb.k_lo >= 1 && hb.k_lo + hb.M <= L && hb.k_lo + reach < L + kFastGuard && 3 * st <= L &&
-                hb.off + reach < p.C + kFastGuard)
-                fast |= kItemFastRoute;
-            if (hb.off + reach < p.C) fast |= kItemFastCoef;
-            for (int s0 = 0; s0 < batch; s0 += G)
-                p.items.push_back(
-                    WorkItem{l, s0, std::min(G, batch - s0), lg, fast, p.banddev[static_cast<size_t>(l)]});
-        }
+        // 2^lg interleaved signals (seq_lg, within the band's matrix-tile cap)
+        for (int32_t l : bk.bands)
+            add_items(bk, l, std::min(seq_lg(work[l], E, batch, row_bytes), fit[l].lg_cap), bk.nt);
         bk.nitems = static_cast<int>(p.items.size()) - bk.item_off;
+    }
+    for (auto& bk : p.buckets)
         if (bk.lds_elems * 8 > 160 * 1024)
             return fail(err, NSGCQT_EUNSUPPORTED, "band kernel exceeds LDS");
-    }
 
     // huge-band work items: pass 0/1 over every huge band, pass 2/3 over the
     // Bluestein ones (their second FFT)

@@ -35,14 +35,16 @@ struct BandSpec {
 // Band kernels are launched per bucket; each bucket has one thread count and
 // one bound on the elements each thread holds per Stockham stage.
 struct Bucket {
-    int nt;               // threads per workgroup
-    int ept;              // elements per thread bound (template parameter)
-    int max_work;         // largest transform length in the bucket
-    int64_t coeffs;       // sum of M over its bands
+    int nt = 0;           // threads per workgroup
+    int ept = 0;          // elements per thread bound (template parameter)
+    int max_work = 0;     // largest transform length in the bucket
+    int64_t coeffs = 0;   // sum of M over its bands
     std::vector<int32_t> bands;
-    int item_off;         // first work item of the bucket in HostPlan::items
-    int nitems;
-    int lds_elems;        // largest data LDS slots over its items
+    int item_off = 0;     // first work item of the bucket in HostPlan::items
+    int nitems = 0;
+    int lds_elems = 0;    // largest data LDS slots over its items
+    double slots = 0.0;   // element slots over its items (the schedule's estimate)
+    bool all = false;     // bands of several tiers in one launch, each item with its own thread count
 };
 
 // Four-step split of the packed FFT: L = L1 * L2. Pass A transforms columns
@@ -89,6 +91,7 @@ struct HostPlan {
     std::vector<float> chirp, kern;         // Bluestein tables
     std::vector<float> slicewin;            // sliced plans: window of length N
     std::vector<Bucket> buckets;
+    bool fan = false;           // long band phase without a launch that fills the GPU (see plan.cpp)
     std::vector<WorkItem> items;
 
     // huge bands (transform above one workgroup): descriptors, work items of

@@ -93,6 +93,7 @@ struct WorkItem {
     int32_t count;
     int32_t lgnb;
     int32_t fast;      // kItemFast* flags
+    int32_t nt;        // threads of the workgroup that work on the item
     BandDev bd;
 };
 

@@ -425,6 +425,40 @@ def test_band_list_against_oracle(case):
     _check_all_ops(p, lay, x, y, xs_, mode=mode)
 
 
+# (name, plan arguments, batch): the one-launch band phase at its edges: items
+# of one wave up to 1024 threads, a block size of 256, 512 and 1024 threads,
+# matrix-core stages with one and several tiles per wave, interleaves 1 to 16
+# with a remainder, Bluestein bands, and the 16,384-point items (16 elements
+# per thread)
+ONE_LAUNCH = [
+    ("block256", (22050.0, 110.0, 11025.0, 12, 16384), 19),
+    ("block512", (16000.0, 50.0, 8000.0, 24, 50274), 3),
+    ("block1024", (44100.0, 40.0, 22050.0, 24, 132300), 2),
+    ("items16k", (44100.0, 40.0, 22050.0, 24, 220500), 1),
+]
+
+
+@pytest.mark.parametrize("case", ONE_LAUNCH, ids=[c[0] for c in ONE_LAUNCH])
+def test_one_launch_band_phase_against_oracle(case):
+    # the band phase is one launch, agrees with the oracle, and a signal's
+    # bits do not depend on the interleave its neighbours give it
+    _, args, b = case
+    lay = oracle.build_layout(*args)
+    p = nb.Plan(*args, batch=b)
+    assert [n for n, _ in p.stage_info(nb.OP_ANALYSE)][2:] == ["band_analysis_all"]
+    assert [n for n, _ in p.stage_info(nb.OP_SYNTHESISE)][:1] == ["band_synthesis_all"]
+    N = args[-1]
+    x, y = workloads.white(N + 15, b, N), workloads.coeff_cotangent(N + 16, b, p.n_coeffs)
+    xs = workloads.signal_cotangent(N + 17, b, N)
+    _check_all_ops(p, lay, x, y, xs, mode="fft")
+    p1 = nb.Plan(*args, batch=1)
+    for i in {0, b - 1}:
+        assert np.array_equal(to_np(p1.analyse(to_gpu(x[i:i + 1])))[0].view(np.uint32),
+                              to_np(p.analyse(to_gpu(x)))[i].view(np.uint32))
+        assert np.array_equal(to_np(p1.synthesise(to_gpu(y[i:i + 1])))[0].view(np.uint32),
+                              to_np(p.synthesise(to_gpu(y)))[i].view(np.uint32))
+
+
 def test_erb_layout_against_oracle():
     # an auditory (ERB-rate) frame through the band-list plan
     fs, N, b = 16000.0, 32000, 2
