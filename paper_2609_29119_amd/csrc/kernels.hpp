@@ -26,6 +26,10 @@ namespace nsg {
 // 80 VGPRs, no spills); the larger tiers do not.
 #define NSG_OCC_BAND __attribute__((amdgpu_waves_per_eu(((NT == 256 || NT == 64) && EPT == 8) ? 6 : 2)))
 
+// The overlap-add pass waits on its gather: six waves per SIMD there too (at
+// 86 VGPRs and five it took 52.4 us instead of 48.3 on 128 x 88,200).
+#define NSG_OCC_INV __attribute__((amdgpu_waves_per_eu(6)))
+
 struct Tables {
     const BandDev* bands;
     const FftDesc* ffts;
@@ -277,7 +281,7 @@ __device__ __forceinline__ float2 retangle_conj(float2 om, float2 xq, float2 xm)
 
 // WIDE: the plan's bin records are the 32-byte form (absolute indices).
 template <int NT, int EPT, bool WIDE>
-__global__ __launch_bounds__(NT) NSG_OCC void k_inv_a(const float2* __restrict__ W, float2* __restrict__ Y,
+__global__ __launch_bounds__(NT) NSG_OCC_INV void k_inv_a(const float2* __restrict__ W, float2* __restrict__ Y,
                                                       Pass p, Tables T, int batch, long long C) {
     extern __shared__ float2 lds[];
     float2 *t4, *buf;
