@@ -348,7 +348,8 @@ OneFit one_fit(int n, int lg_cap, int ept, int block, int batch, int64_t row_byt
 //    than the waits: 64 x 88,200 215 us in one launch, 208 us by tier; 48 x
 //    177 and 183 us.
 //  - Long phases without a launch that fills the GPU fan out over streams
-//    (see the schedule). Beside a huge-band chain, which is the longest of
+//    (see the schedule), and so does a huge-band chain with its neighbour
+//    launch: 1 x 1,000,000 at 48 bands per octave 202 -> 173 us. Beside a huge-band chain, which is the longest of
 //    their units, the tiers share one launch: two forks fewer (1 x 2,880,000
 //    365 -> 341 us, 6 x 500,000 285 -> 270 us). The 16,384-point tier joins
 //    it for up to two items per compute unit, since every workgroup then
@@ -373,6 +374,7 @@ int plan_launches(HostPlan& p, const std::vector<int>& work, const std::vector<B
     const bool is_long = slots >= kLongPhase;
     p.fan = is_long && most < 2048;
     if (p.bands.size() < 32) return 0;
+    p.fan = p.fan || !p.bigs.empty();
     if (!is_long) return 16384;
     if (p.fan && !p.bigs.empty()) return items <= 512 ? 16384 : 8192;
     return 0;
@@ -939,7 +941,7 @@ int finish_plan(HostPlan& p, std::string& err) {
     auto add_items = [&](Bucket& bk, int32_t l, int lg, int nt) {
         const int n = work[l], G = 1 << lg;
         bk.lds_elems = std::max(bk.lds_elems, lds_slots(n, lg));
-        bk.slots += static_cast<double>((batch + G - 1) / G) * (bk.all ? static_cast<double>(n) * G : static_cast<double>(bk.nt) * bk.ept);
+        bk.slots += static_cast<double>((batch + G - 1) / G) * (static_cast<double>(bk.nt) * bk.ept);
         // fast load phases (WorkItem flags): every read up to entry
         // M - 1 + 3 st of the band stays in the data or the guards
         const auto& hb = p.bands[static_cast<size_t>(l)];
