@@ -158,7 +158,6 @@ int upload(nsgcqt_plan_s* p) {
     const size_t iLo = add(h.tw4_lo.data(), h.tw4_lo.size() * sizeof(float));
     const size_t iWin = add(h.slicewin.data(), h.slicewin.size() * sizeof(float));
     const size_t iItems = add(h.items.data(), h.items.size() * sizeof(WorkItem));
-    const size_t iBigs = add(h.bigs.data(), h.bigs.size() * sizeof(BigDesc));
     const size_t iBigItems = add(h.bigitems.data(), h.bigitems.size() * sizeof(BigItem));
     const size_t iWA = add(h.wA.data(), h.wA.size() * sizeof(float), g1);
     const size_t iWS = add(h.wS.data(), h.wS.size() * sizeof(float), g1);
@@ -190,7 +189,6 @@ int upload(nsgcqt_plan_s* p) {
     T.tw4_lo = static_cast<const float2*>(at(iLo));
     T.slicewin = static_cast<const float*>(at(iWin));
     T.items = static_cast<const WorkItem*>(at(iItems));
-    T.bigs = static_cast<const BigDesc*>(at(iBigs));
     T.bigitems = static_cast<const BigItem*>(at(iBigItems));
     p->wA = static_cast<const float*>(at(iWA));
     p->wS = static_cast<const float*>(at(iWS));
@@ -211,8 +209,9 @@ int upload(nsgcqt_plan_s* p) {
 
 // Launch schedule of the band phase, from the host plan alone. Overlap pays
 // when no band launch fills the GPU by itself and the band phase is long
-// against the fork and join (~25 us each way): the plan's fan flag. Then units are enqueued longest first, each onto the least
-// loaded of the four streams; otherwise in bucket order on the caller's.
+// against the fork and join (~25 us each way): the plan's fan flag. Then units
+// are enqueued longest first, each onto the least loaded of the four streams;
+// otherwise in bucket order on the caller's.
 void schedule(nsgcqt_plan_s* p) {
     const HostPlan& h = p->h;
     std::vector<double> cost;

@@ -349,12 +349,14 @@ OneFit one_fit(int n, int lg_cap, int ept, int block, int batch, int64_t row_byt
 //    177 and 183 us.
 //  - Long phases without a launch that fills the GPU fan out over streams
 //    (see the schedule), and so does a huge-band chain with its neighbour
-//    launch: 1 x 1,000,000 at 48 bands per octave 202 -> 173 us. Beside a huge-band chain, which is the longest of
-//    their units, the tiers share one launch: two forks fewer (1 x 2,880,000
-//    365 -> 341 us, 6 x 500,000 285 -> 270 us). The 16,384-point tier joins
-//    it for up to two items per compute unit, since every workgroup then
-//    reserves 128 KB of LDS (1 x 2,000,000 284 -> 270 us; beyond, 3 x
-//    1,000,000 300 -> 309 us).
+//    launch: 1 x 1,000,000 at 48 bands per octave 202 -> 173 us. Merging the
+//    tiers there as well moves 16 x 220,500 236 -> 229 to 246 us and 24 x
+//    220,500 at 36 bands per octave 265 -> 283 to 362 us by how much is merged.
+//  - Beside a huge-band chain, which is the longest of their units, the tiers
+//    share one launch: two forks fewer (1 x 2,880,000 365 -> 341 us, 6 x
+//    500,000 285 -> 270 us). The 16,384-point tier joins it for up to two
+//    items per compute unit, since every workgroup then reserves 128 KB of LDS
+//    (1 x 2,000,000 284 -> 270 us; beyond, 3 x 1,000,000 300 -> 309 us).
 //  - Plans of fewer than 32 bands keep their tiers: there is little to merge.
 int plan_launches(HostPlan& p, const std::vector<int>& work, const std::vector<BandFit>& fit, int64_t row_bytes) {
     double slots = 4.0 * static_cast<double>(p.Hn) * static_cast<double>(p.batch);
@@ -921,6 +923,9 @@ int finish_plan(HostPlan& p, std::string& err) {
             p.C_big += p.bands[l].M;
             if (p.banddev[l].chirp >= 0) { p.Hn_blu += n; p.C_big_blu += p.bands[l].M; }
             const FftDesc& fn = p.ffts[g.fftn];
+            g.tw4 = fn.full + fn.n;
+            g.nhi = fn.nhi;
+            g.lg4 = fn.lg;
             big_t4 = std::max(big_t4, fn.nhi + (1 << fn.lg));
             big_ea = std::max(big_ea, lds_slots(g.n1, g.lga));
             big_eb = std::max(big_eb, lds_slots(g.n2, g.lgb));
@@ -1017,7 +1022,7 @@ int finish_plan(HostPlan& p, std::string& err) {
             if (pass >= 2 && p.banddev[g.band].chirp < 0) continue;
             const int tiles = (pass % 2 == 0) ? (g.n2 + (1 << g.lga) - 1) >> g.lga : (g.n1 + (1 << g.lgb) - 1) >> g.lgb;
             for (int sg = 0; sg < batch; ++sg)
-                for (int t = 0; t < tiles; ++t) p.bigitems.push_back(BigItem{static_cast<int32_t>(gi), sg, t, 0});
+                for (int t = 0; t < tiles; ++t) p.bigitems.push_back(BigItem{sg, t, g, p.banddev[g.band]});
         }
         p.big_n[pass] = static_cast<int>(p.bigitems.size()) - p.big_off[pass];
     }

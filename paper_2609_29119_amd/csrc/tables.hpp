@@ -117,15 +117,16 @@ struct BigDesc {
     int32_t fft1, fft2;      // FftDescs of the column (n1) and row (n2) transforms
     int32_t lga, lgb;        // log2 of the columns / rows per workgroup
     int32_t hoff;
-    int32_t pad;
+    int32_t tw4, nhi, lg4;   // the two-level table of n: pool offset, hi values, log2 of the lo values
 };
 
-// One workgroup of a huge-band pass: band big, signal sig, tile index tile.
+// One workgroup of a huge-band pass: signal sig, tile index tile of the band
+// described by bg and bd (repeated here, as in WorkItem).
 struct BigItem {
-    int32_t big;
     int32_t sig;
     int32_t tile;
-    int32_t pad;
+    BigDesc bg;
+    BandDev bd;
 };
 
 // Largest prime factor of n above 16 (the radix of a matrix-core stage), or 0.
