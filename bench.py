@@ -258,7 +258,7 @@ def stage_of_kernel(name):
     if re.search(r"\bk_ola\b", name):
         return "sliced_overlap_add"
     m = re.search(r"k_(fwd_a|inv_a|pass_b|band_analysis(?:_all)?|band_synthesis(?:_all)?|big_a|big_b)"
-                  r"<(\d+), (\d+)(?:, (true|false))?>", name)
+                  r"<(\d+), (\d+)(?:, (true|false|\d+))?>", name)
     if not m:
         return None
     k, nt, ept, inv = m.groups()

@@ -975,9 +975,10 @@ __global__ __launch_bounds__(NT) NSG_OCC void k_big_a(BigArgs a, Tables T, int i
 // other band finishes; second == 1: the Bluestein band finishes. Reads are
 // batched as in the column pass; the outputs k >= M of a Bluestein band's last
 // transform are not visited.
-template <int NT, int EPT>
-__global__ __launch_bounds__(NT) NSG_OCC void k_big_b(BigArgs a, Tables T, int item0, int nitems, int batch,
-                                                      int second) {
+template <int NT, int EPT, int OCC>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC))) void k_big_b(BigArgs a, Tables T, int item0,
+                                                                                        int nitems, int batch,
+                                                                                        int second) {
     extern __shared__ float2 lds[];
     const BigItem it = T.bigitems[item0 + xcd_remap(blockIdx.x, nitems)];
     if (it.sig >= batch) return;

@@ -492,21 +492,33 @@ int run_bucket(nsgcqt_plan_s* p, size_t bi, bool analysis, const float2* in, flo
 int run_big(nsgcqt_plan_s* p, BigArgs a, int batch, hipStream_t s) {
     const HostPlan& h = p->h;
     if (h.bigs.empty()) return NSGCQT_OK;
-    auto ka = k_big_a<512, 8>;
-    auto kb = k_big_b<512, 8>;
-    if (int r = launch_prep(ka, h.big_lds_a)) return r;
-    if (int r = launch_prep(kb, h.big_lds_b)) return r;
     const int in0 = a.analysis ? kBigInRoute : kBigInCoef;
+    // At seven waves per SIMD (70 registers) the row pass holds three workgroups
+    // per compute unit; a larger grid would leave a nearly empty second round, so
+    // it takes the kernel at eight waves and four workgroups (round trips of
+    // 1 x 2,880,000 327 -> 319 us, 3 x 1,000,000 320 -> 316 us, 1 x 2,000,000
+    // 297 -> 292 us; 1 x 1,000,000, fewer workgroups, 170 us at seven and 172
+    // at eight). The column pass spills at eight.
+    constexpr int kThreePerCu = 3 * 256;
     for (int pass = 0; pass < 4; ++pass) {
         const int n = h.big_n[pass];
         if (n == 0) continue;
-        ev_start(p, s);
-        if (pass % 2 == 0)
-            LAUNCH_TRY(ka, dim3(n), dim3(512), h.big_lds_a, s, a, p->T, h.big_off[pass], n, batch,
+        auto columns = [&](auto k) -> int {
+            if (int r = launch_prep(k, h.big_lds_a)) return r;
+            LAUNCH_TRY(k, dim3(n), dim3(512), h.big_lds_a, s, a, p->T, h.big_off[pass], n, batch,
                        pass == 0 ? in0 : kBigInBlu2);
-        else
-            LAUNCH_TRY(kb, dim3(n), dim3(512), h.big_lds_b, s, a, p->T, h.big_off[pass], n, batch,
+            return NSGCQT_OK;
+        };
+        auto rows = [&](auto k) -> int {
+            if (int r = launch_prep(k, h.big_lds_b)) return r;
+            LAUNCH_TRY(k, dim3(n), dim3(512), h.big_lds_b, s, a, p->T, h.big_off[pass], n, batch,
                        pass == 3 ? 1 : 0);
+            return NSGCQT_OK;
+        };
+        ev_start(p, s);
+        if (int r = pass % 2 == 0 ? columns(k_big_a<512, 8>)
+                                  : (n > kThreePerCu ? rows(k_big_b<512, 8, 8>) : rows(k_big_b<512, 8, 2>)))
+            return r;
         ev_end(p, s);
     }
     return NSGCQT_OK;
