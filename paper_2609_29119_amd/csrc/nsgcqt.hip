@@ -123,6 +123,7 @@ struct nsgcqt_plan_s {
     bool fan = false;
     // launch units: the buckets, then the huge-band chain (when there are huge bands)
     std::vector<int> lane;    // stream of each unit: 0 = caller's
+    int lanes = 1;            // streams in use, the caller's among them
     std::vector<int> order;   // enqueue order of the units
     // the enqueue state above (events, the resident-block cache, the fork and
     // join events) is used by one call at a time
@@ -229,6 +230,7 @@ void schedule(nsgcqt_plan_s* p) {
         for (int k = 1; k <= nsgcqt_plan_s::kSide; ++k)
             if (load[k] < load[best]) best = k;
         p->lane[u] = best;
+        p->lanes = std::max(p->lanes, best + 1);
         load[best] += cost[u];
     }
 }
@@ -260,10 +262,32 @@ struct Fanout {
     hipStream_t s;
     bool forked = false;
     bool used[nsgcqt_plan_s::kSide] = {};
+    // A side stream joins the capture of a captured call and stays in it until
+    // that capture ends. A call on any other stream meanwhile (eager, or in a
+    // capture of its own) would put its work into the open capture, so it runs
+    // on s alone. The caller's stream is asked only then: the default stream
+    // cannot be asked while another stream captures, nor can it capture.
+    int sides_free(bool* yes) {
+        *yes = true;
+        bool known = false;
+        hipStreamCaptureStatus mine = hipStreamCaptureStatusNone, st = hipStreamCaptureStatusNone;
+        unsigned long long my_id = 0, id = 0;
+        for (int i = 0; i < p->lanes - 1 && *yes; ++i) {
+            HIP_TRY(hipStreamGetCaptureInfo(p->side[i], &st, &id));
+            if (st == hipStreamCaptureStatusNone) continue;
+            if (!known && s) HIP_TRY(hipStreamGetCaptureInfo(s, &mine, &my_id));
+            known = true;
+            *yes = st == hipStreamCaptureStatusActive && mine == hipStreamCaptureStatusActive && id == my_id;
+        }
+        return NSGCQT_OK;
+    }
     // the fork point precedes every launch of the phase, including those
     // that go on s itself
     int begin() {
         if (!p->fan) return NSGCQT_OK;
+        bool ok = false;
+        if (int r = sides_free(&ok)) return r;
+        if (!ok) return NSGCQT_OK;
         HIP_TRY(hipEventRecord(p->fork_ev, s));
         forked = true;
         return NSGCQT_OK;

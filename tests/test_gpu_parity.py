@@ -573,6 +573,44 @@ def test_graph_capture_with_side_streams():
         assert np.array_equal(to_np(xr).view(np.uint32), xe.view(np.uint32)), i
 
 
+@pytest.mark.parametrize("args,batch", [((48000.0, 40.0, 24000.0, 12, 240000), 1),
+                                        ((44100.0, 40.0, 22050.0, 24, 220500), 16)],
+                         ids=["short_with_chain", "long"])
+def test_calls_beside_an_open_capture(args, batch):
+    # while a captured call of a plan that forks is still being captured, the
+    # same plan takes an eager call on another stream and a second capture
+    # there: neither joins the first capture, and all three results are the
+    # eager call's bit for bit
+    N = args[-1]
+    p = nb.Plan(*args, batch=batch)
+    x = [to_gpu(workloads.white(61 + i, batch, N)) for i in range(3)]
+    ref = [to_np(p.analyse(v)) for v in x]
+    out = [torch.zeros((batch, p.n_coeffs), dtype=torch.complex64, device="cuda") for _ in x]
+    ws = [torch.empty(p.info.ws_analyse, dtype=torch.uint8, device="cuda") for _ in x]
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g, g2 = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="relaxed"):
+        p.analyse(x[0], out=out[0], ws=ws[0])
+        p.analyse(x[1], out=out[1], ws=ws[1], stream=other)
+        other.synchronize()
+        with torch.cuda.stream(other):
+            g2.capture_begin(capture_error_mode="relaxed")
+            p.analyse(x[2], out=out[2], ws=ws[2], stream=other)
+            g2.capture_end()
+        p.analyse(x[0], out=out[0], ws=ws[0])      # the first capture goes on
+    assert np.array_equal(to_np(out[1]).view(np.uint32), ref[1].view(np.uint32))
+    for _ in range(3):
+        for i in (0, 2):
+            out[i].zero_()
+        p.analyse(x[1], out=out[1], ws=ws[1])      # and forks again afterwards
+        torch.cuda.synchronize()
+        g.replay()
+        g2.replay()
+        for i in range(3):
+            assert np.array_equal(to_np(out[i]).view(np.uint32), ref[i].view(np.uint32)), i
+
+
 def test_stage_events_bracket_every_launch_with_side_streams():
     # with the band phase fanned out over the side streams, the i-th event
     # pair brackets the i-th kernel of nsgcqt_stage_info on the stream that
