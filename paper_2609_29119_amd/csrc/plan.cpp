@@ -946,7 +946,14 @@ int finish_plan(HostPlan& p, std::string& err) {
     auto add_items = [&](Bucket& bk, int32_t l, int lg, int nt) {
         const int n = work[l], G = 1 << lg;
         bk.lds_elems = std::max(bk.lds_elems, lds_slots(n, lg));
-        bk.slots += static_cast<double>((batch + G - 1) / G) * (static_cast<double>(bk.nt) * bk.ept);
+        // A shared launch's items count with their own threads. Counted with its
+        // block's, a launch of many one-wave items passed for longer than the
+        // huge-band chain, which was then forked off behind it (1 x 1,000,000 at
+        // 48 bands per octave 168.4 us a round trip, 162.2 by the items' threads).
+        // Counted with its elements alone it falls behind the 16,384-point tier,
+        // which costs more than it should (8 x 240,000 at 12 bands per octave
+        // 202 -> 212 us, 4 x 500,000 at 24 225 -> 237 us, 1 x 2,880,000 319 -> 325).
+        bk.slots += static_cast<double>((batch + G - 1) / G) * (static_cast<double>(nt) * bk.ept);
         // fast load phases (WorkItem flags): every read up to entry
         // M - 1 + 3 st of the band stays in the data or the guards
         const auto& hb = p.bands[static_cast<size_t>(l)];

@@ -429,6 +429,20 @@ def test_stage_order_follows_the_launch_schedule(lib):
     assert syn == [n.replace("analysis", "synthesis") for n in an[2:]] + ["fft_inv_a_overlap_add", "fft_inv_b"]
 
 
+@pytest.mark.parametrize("args,batch,rest", [
+    ((44100.0, 40.0, 22050.0, 48, 1000000), 1, ["all"]),
+    ((48000.0, 40.0, 24000.0, 12, 240000), 1, ["all"]),
+    ((48000.0, 40.0, 24000.0, 12, 240000), 8, ["all", "1024x16"]),
+    ((48000.0, 20.0, 24000.0, 96, 2880000), 1, ["all", "1024x16"]),
+])
+def test_huge_band_chain_is_enqueued_before_the_shared_launch(lib, args, batch, rest):
+    # the huge-band chain (four launches in series) is the longest unit of
+    # these plans, ahead of the launch that the smaller tiers share
+    names = [n for n, _ in nb.Plan(*args, batch=batch, device=False).stage_info(nb.OP_ANALYSE)][2:]
+    assert names == ["big_analysis_a", "big_analysis_b", "big_analysis_a2", "big_analysis_b2"] + \
+        ["band_analysis_" + r for r in rest]
+
+
 def test_sliced_stage_info_lists_one_chunk(lib):
     # a sliced plan reports the kernels of one chunk of slices: the analysis
     # chain, and the synthesis chain followed by the overlap-add
