@@ -357,7 +357,14 @@ OneFit one_fit(int n, int lg_cap, int ept, int block, int batch, int64_t row_byt
 //    500,000 285 -> 270 us). The 16,384-point tier joins it for up to two
 //    items per compute unit, since every workgroup then reserves 128 KB of LDS
 //    (1 x 2,000,000 284 -> 270 us; beyond, 3 x 1,000,000 300 -> 309 us).
-//  - Plans of fewer than 32 bands keep their tiers: there is little to merge.
+//  - Plans of up to 16 bands keep a launch per tier. Speed does not draw this
+//    line: one launch is the faster form down to the smallest layouts measured
+//    (28 bands, 1 x 32,000 133 -> 52 us; 24 bands with a chain, 1 x 400,000
+//    294 -> 147 us; 17 bands with a chain, 1 x 132,300 214 -> 118 us; 12 bands
+//    243 -> 125 us, 14 bands, 4 x 16,384 101 -> 65 us). It is where short
+//    hand-written band lists stay, a way to run each tier's own kernel on a
+//    small input. Their chain overlaps the tiers all the same (12 bands 243 -> 147
+//    to 178 us by run, 11 bands, 8 x 80,000 250 -> 188 us).
 int plan_launches(HostPlan& p, const std::vector<int>& work, const std::vector<BandFit>& fit, int64_t row_bytes) {
     double slots = 4.0 * static_cast<double>(p.Hn) * static_cast<double>(p.batch);
     int64_t items = 0, most = 0;
@@ -374,11 +381,10 @@ int plan_launches(HostPlan& p, const std::vector<int>& work, const std::vector<B
         most = std::max(most, here);
     }
     const bool is_long = slots >= kLongPhase;
-    p.fan = is_long && most < 2048;
-    if (p.bands.size() < 32) return 0;
-    p.fan = p.fan || !p.bigs.empty();
+    p.fan = (is_long && most < 2048) || !p.bigs.empty();
+    if (p.bands.size() <= 16) return 0;
     if (!is_long) return 16384;
-    if (p.fan && !p.bigs.empty()) return items <= 512 ? 16384 : 8192;
+    if (!p.bigs.empty()) return items <= 512 ? 16384 : 8192;
     return 0;
 }
 

@@ -429,6 +429,26 @@ def test_stage_order_follows_the_launch_schedule(lib):
     assert syn == [n.replace("analysis", "synthesis") for n in an[2:]] + ["fft_inv_a_overlap_add", "fft_inv_b"]
 
 
+@pytest.mark.parametrize("fs,fmin,bpo,n,batch,units", [
+    (22050.0, 2800.0, 12, 16384, 1, ["all"]),                   # 26 bands
+    (44100.0, 40.0, 3, 44100, 8, ["all"]),                      # 30 bands
+    (44100.0, 40.0, 3, 132300, 1, ["chain", "all"]),            # 30 bands, huge ones
+    (44100.0, 690.0, 3, 132300, 1, ["chain", "all"]),           # 17 bands, huge ones
+    (44100.0, 690.0, 2, 132300, 1, ["chain", "512x16", "1024x16", "256x16", "256x8"]),   # 12 bands
+    (22050.0, 5600.0, 12, 16384, 4, ["64x8", "256x8", "1024x16"]),                       # 14 bands
+])
+def test_launches_of_layouts_with_few_bands(lib, fs, fmin, bpo, n, batch, units):
+    # short band phases are one launch from 17 bands on; a huge-band chain
+    # overlaps the other launches (and so goes first) at any number of bands
+    p = nb.Plan(fs, fmin, fs / 2, bpo, n, batch=batch, device=False)
+    names = [x.replace("band_analysis_", "") for x, _ in p.stage_info(nb.OP_ANALYSE)][2:]
+    chain = [x for x in names if x.startswith("big_analysis")]
+    if chain:
+        assert names[:len(chain)] == chain
+        names = ["chain"] + names[len(chain):]
+    assert names == units
+
+
 @pytest.mark.parametrize("args,batch,rest", [
     ((44100.0, 40.0, 22050.0, 48, 1000000), 1, ["all"]),
     ((48000.0, 40.0, 24000.0, 12, 240000), 1, ["all"]),

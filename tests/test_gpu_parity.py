@@ -435,6 +435,7 @@ ONE_LAUNCH = [
     ("block512", (16000.0, 50.0, 8000.0, 24, 50274), 3),
     ("block1024", (44100.0, 40.0, 22050.0, 24, 132300), 2),
     ("items16k", (44100.0, 40.0, 22050.0, 24, 220500), 1),
+    ("bands30", (44100.0, 40.0, 22050.0, 3, 44100), 3),
 ]
 
 
