@@ -434,7 +434,7 @@ def test_stage_order_follows_the_launch_schedule(lib):
     (44100.0, 40.0, 3, 44100, 8, ["all"]),                      # 30 bands
     (44100.0, 40.0, 3, 132300, 1, ["chain", "all"]),            # 30 bands, huge ones
     (44100.0, 690.0, 3, 132300, 1, ["chain", "all"]),           # 17 bands, huge ones
-    (44100.0, 690.0, 2, 132300, 1, ["chain", "512x16", "1024x16", "256x16", "256x8"]),   # 12 bands
+    (44100.0, 690.0, 2, 132300, 1, ["chain", "1024x16", "256x16", "512x16", "256x8"]),   # 12 bands
     (22050.0, 5600.0, 12, 16384, 4, ["64x8", "256x8", "1024x16"]),                       # 14 bands
 ])
 def test_launches_of_layouts_with_few_bands(lib, fs, fmin, bpo, n, batch, units):
