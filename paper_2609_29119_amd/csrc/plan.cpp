@@ -126,12 +126,15 @@ struct FftRegistry {
     explicit FftRegistry(HostPlan& plan) : p(plan) {}
 
     // Index of the FftDesc for length n, creating it (and its twiddles) on
-    // first use; -1 if n does not factor into supported radices.
+    // first use; -1 if n does not factor into supported radices or, for a
+    // workgroup's transform, has more stages than the kernels hold in LDS.
     int get(int64_t n) {
         auto it = index.find(n);
         if (it != index.end()) return it->second;
         std::vector<int> rad;
         if (!factor_radices(n, rad)) return -1;
+        // a workgroup's transform keeps its stage records in an LdsDesc
+        if (n <= kMaxLdsFft && rad.size() > static_cast<size_t>(kLdsStages)) return -1;
         FftDesc d{};
         d.n = static_cast<int32_t>(n);
         d.nstages = static_cast<int32_t>(rad.size());

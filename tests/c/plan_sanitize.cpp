@@ -91,6 +91,14 @@ int main() {
         std::vector<BandSpec> s = {{0, h, 2.0, N, 0.0}, {1, h, 2.0, 0, 0.0}, {2, h, 2.0, 0, 0.0}};
         bl(48000.0, N, 1, s, false, true);
     }
+    // every length a workgroup may transform fits the kernels' stage records
+    for (int n = 1; n <= kMaxLdsFft; ++n) {
+        std::vector<int> rad;
+        if (factor_radices(n, rad) && rad.size() > static_cast<size_t>(kLdsStages)) {
+            printf("UNEXPECTED stages n=%d %zu\n", n, rad.size());
+            ++n_bad;
+        }
+    }
     printf("plans ok %d, rejected %d, unexpected %d\n", n_ok, n_err, n_bad);
     return n_bad ? 1 : 0;
 }
