@@ -31,12 +31,9 @@ namespace nsg {
 #define NSG_OCC_INV __attribute__((amdgpu_waves_per_eu(6)))
 
 struct Tables {
-    const BandDev* bands;
     const FftDesc* ffts;
     const float2* tw;        // twiddle pool
     const float2* omega;     // exp(-2 pi i k / N), k = 0..L
-    const int32_t* owner;    // first band covering bin k | count << 24, k = 0..L
-    const int32_t* bandbase; // off - k_lo per band
     const int4* gather;      // per bin k = 0..L: covering bands of k and of L - k (one or two int4)
     const float2* chirp;     // Bluestein exp(-i pi m^2 / M)
     const float2* kern;      // Bluestein DFT_P(b) / P

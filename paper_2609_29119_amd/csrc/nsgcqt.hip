@@ -146,12 +146,9 @@ int upload(nsgcqt_plan_s* p) {
         return ch.size() - 1;
     };
     const int64_t g1 = kFastGuard * static_cast<int64_t>(sizeof(float)), g4 = 4 * g1;
-    const size_t iBands = add(h.banddev.data(), h.banddev.size() * sizeof(BandDev));
     const size_t iFfts = add(h.ffts.data(), h.ffts.size() * sizeof(FftDesc));
     const size_t iTw = add(h.twpool.data(), h.twpool.size() * sizeof(float));
     const size_t iOm = add(h.omega.data(), h.omega.size() * sizeof(float));
-    const size_t iOwn = add(h.owner.data(), h.owner.size() * sizeof(int32_t));
-    const size_t iBase = add(h.bandbase.data(), h.bandbase.size() * sizeof(int32_t));
     const size_t iGather = add(h.gather.data(), h.gather.size() * sizeof(int32_t));
     const size_t iCh = add(h.chirp.data(), h.chirp.size() * sizeof(float), 2 * g1);
     const size_t iK = add(h.kern.data(), h.kern.size() * sizeof(float));
@@ -177,12 +174,9 @@ int upload(nsgcqt_plan_s* p) {
         if (c.bytes > 0) HIP_TRY(hipMemcpy(d + c.off, c.src, c.bytes, hipMemcpyHostToDevice));
     auto at = [&](size_t i) { return static_cast<const void*>(d + ch[i].off); };
     Tables& T = p->T;
-    T.bands = static_cast<const BandDev*>(at(iBands));
     T.ffts = static_cast<const FftDesc*>(at(iFfts));
     T.tw = static_cast<const float2*>(at(iTw));
     T.omega = static_cast<const float2*>(at(iOm));
-    T.owner = static_cast<const int32_t*>(at(iOwn));
-    T.bandbase = static_cast<const int32_t*>(at(iBase));
     T.gather = static_cast<const int4*>(at(iGather));
     T.chirp = static_cast<const float2*>(at(iCh));
     T.kern = static_cast<const float2*>(at(iK));
