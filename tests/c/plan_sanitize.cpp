@@ -1,7 +1,9 @@
 // The host planner (plan.cpp) under AddressSanitizer, UBSan and libstdc++
 // bounds assertions, over the workloads, the test layouts and the rejected
 // inputs of the test suite. Prints one summary line; any sanitizer report or
-// unexpected status makes the run fail.
+// unexpected status makes the run fail. Every accepted plan's band launches are
+// checked against what keeps the kernels in range (see check_items).
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <string>
@@ -10,6 +12,79 @@
 using namespace nsg;
 
 static int n_ok = 0, n_err = 0, n_bad = 0;
+
+// What the band kernels rely on: an item's elements fit its threads, its
+// threads are whole waves of the launch's block (all of it in a tier's launch),
+// its matrix-core tiles fit its waves, its sequences fit the launch's LDS, the
+// paired load forms stay inside data plus guard, no prime stage in a Bluestein
+// length (its first stage takes the kernel's product), and every band of every
+// signal is transformed once.
+static void check_items(const HostPlan& p, const char* what) {
+    auto bad = [&](const char* why, size_t at) {
+        printf("UNEXPECTED %s: %s at %zu\n", what, why, at);
+        ++n_bad;
+    };
+    std::vector<int> seen(p.bands.size() * static_cast<size_t>(p.batch), 0);
+    size_t total = 0;
+    for (const Bucket& bk : p.buckets) {
+        if (bk.lds_elems * 8 > 160 * 1024) bad("reserved LDS", 0);
+        total += static_cast<size_t>(bk.nitems);
+        for (int i = bk.item_off; i < bk.item_off + bk.nitems; ++i) {
+            const WorkItem& w = p.items[static_cast<size_t>(i)];
+            const size_t at = static_cast<size_t>(i);
+            const FftDesc& d = p.ffts[static_cast<size_t>(w.bd.fft)];
+            if (w.nt % 64 || w.nt < 64 || w.nt > bk.nt || (!bk.all && w.nt != bk.nt)) bad("threads", at);
+            if ((static_cast<int64_t>(w.bd.n) << w.lgnb) > static_cast<int64_t>(w.nt) * bk.ept) bad("elements", at);
+            if (lds_slots(w.bd.n, w.lgnb) > bk.lds_elems) bad("LDS", at);
+            if (d.n != w.bd.n || d.nstages > kLdsStages) bad("descriptor", at);
+            for (int s = 0; s < d.nstages; ++s) {
+                const int R = d.st[s].R;
+                if (R <= 16) continue;
+                if (w.bd.chirp >= 0) bad("prime stage in a Bluestein length", at);
+                if (mfma_tiles((w.bd.n / R) << w.lgnb, R) > kMfmaTilesPerWave * (w.nt / 64)) bad("tiles", at);
+            }
+            const int64_t st = w.nt >> w.lgnb, reach = w.bd.M - 1 + 3 * st;
+            if ((w.fast & kItemFastRoute) && (w.bd.k_lo < 1 || w.bd.k_lo + w.bd.M > p.L || 3 * st > p.L ||
+                                              w.bd.k_lo + reach >= p.L + kFastGuard || w.bd.off + reach >= p.C + kFastGuard))
+                bad("paired router reads", at);
+            if ((w.fast & kItemFastCoef) && w.bd.off + reach >= p.C) bad("paired coefficient reads", at);
+            if (w.count < 1 || w.count > (1 << w.lgnb) || w.s0 < 0 || w.s0 + w.count > p.batch) {
+                bad("signals", at);
+                continue;
+            }
+            for (int k = 0; k < w.count; ++k) ++seen[static_cast<size_t>(w.band) * p.batch + w.s0 + k];
+        }
+    }
+    if (total != p.items.size()) bad("items outside the launches", total);
+    // huge bands: every tile of every signal in the column and row pass, and
+    // again in the second transform of a Bluestein band
+    for (int pass = 0; pass < 4; ++pass) {
+        size_t want = 0;
+        for (const BigDesc& g : p.bigs) {
+            const bool blu = p.banddev[static_cast<size_t>(g.band)].chirp >= 0;
+            if (pass >= 2 && !blu) continue;
+            const int n = pass % 2 ? g.n1 : g.n2, lg = pass % 2 ? g.lgb : g.lga;
+            want += static_cast<size_t>((n + (1 << lg) - 1) >> lg) * static_cast<size_t>(p.batch);
+            if (pass == 0)
+                for (int k = 0; k < p.batch; ++k) ++seen[static_cast<size_t>(g.band) * p.batch + k];
+        }
+        if (want != static_cast<size_t>(p.big_n[pass])) bad("huge-band items", static_cast<size_t>(pass));
+    }
+    for (size_t i = 0; i < seen.size(); ++i)
+        if (seen[i] != 1) bad("coverage", i);
+}
+// The shared launch of a plan: threads of its block and elements per thread.
+static void shared(double fs, double fmin, int B, int64_t N, int batch, int nt, int ept) {
+    HostPlan p; std::string err;
+    const int r = build_host_plan(p, fs, fmin, fs / 2, B, N, batch, false, err);
+    const Bucket* all = nullptr;
+    for (const Bucket& bk : p.buckets)
+        if (bk.all) all = &bk;
+    if (r != 0 || !all || all->nt != nt || all->ept != ept) {
+        printf("UNEXPECTED shared launch N=%lld: %dx%d\n", (long long)N, all ? all->nt : 0, all ? all->ept : 0);
+        ++n_bad;
+    }
+}
 static void cq(double fs, double fmin, double fmax, int B, int64_t N, int batch, bool sliced, bool expect_ok) {
     HostPlan p; std::string err;
     int r = build_host_plan(p, fs, fmin, fmax, B, N, batch, sliced, err);
@@ -17,6 +92,7 @@ static void cq(double fs, double fmin, double fmax, int B, int64_t N, int batch,
         printf("UNEXPECTED cq fs=%g N=%lld B=%d r=%d %s\n", fs, (long long)N, B, r, err.c_str());
         ++n_bad;
     }
+    if (r == 0) check_items(p, "cq");
     (r == 0 ? n_ok : n_err)++;
 }
 static void bl(double fs, int64_t N, int batch, const std::vector<BandSpec>& s, bool sliced, bool expect_ok) {
@@ -26,6 +102,7 @@ static void bl(double fs, int64_t N, int batch, const std::vector<BandSpec>& s, 
         printf("UNEXPECTED bands N=%lld r=%d %s\n", (long long)N, r, err.c_str());
         ++n_bad;
     }
+    if (r == 0) check_items(p, "bands");
     (r == 0 ? n_ok : n_err)++;
 }
 static std::vector<BandSpec> padded(const std::vector<double>& xs, const std::vector<int64_t>& lens, int64_t dc, int64_t ny) {
@@ -57,6 +134,25 @@ int main() {
     cq(22050, 110, 11025, 12, 16384, 3, false, true);
     // coarse long layout (wide gather records)
     cq(44100, 20, 22050, 12, 1323000, 1, false, true);
+    // shared band launches: each block size, with and without 16 elements per
+    // thread, beside a huge-band chain, few bands, long phases
+    shared(22050, 110, 12, 16384, 19, 256, 8);
+    shared(16000, 50, 24, 50274, 3, 512, 8);
+    shared(44100, 40, 24, 132300, 2, 1024, 8);
+    shared(44100, 40, 24, 220500, 3, 1024, 16);
+    shared(44100, 40, 3, 44100, 3, 1024, 16);
+    shared(48000, 40, 12, 240000, 1, 1024, 16);
+    shared(48000, 40, 12, 240000, 8, 1024, 8);
+    cq(22050, 110, 11025, 12, 16384, 19, false, true);
+    cq(16000, 50, 8000, 24, 50274, 3, false, true);
+    cq(44100, 40, 22050, 24, 132300, 2, false, true);
+    cq(44100, 40, 22050, 24, 220500, 3, false, true);
+    cq(44100, 40, 22050, 3, 44100, 3, false, true);
+    cq(44100, 690, 22050, 3, 132300, 5, false, true);
+    cq(48000, 40, 24000, 12, 240000, 1, false, true);
+    cq(48000, 40, 24000, 12, 240000, 8, false, true);
+    cq(44100, 40, 22050, 48, 220500, 7, false, true);
+    cq(8000, 31, 4000, 17, 65522, 11, false, true);
     // errors
     cq(22050, 110, 11025, 12, 16383, 1, false, false);   // odd N
     cq(22050, 110, 11025, 12, 2, 1, false, false);       // N < 4
