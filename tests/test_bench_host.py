@@ -23,11 +23,15 @@ def test_more_than_one_gpu_is_refused():
     ("void nsg::k_fwd_a<512, 8, false>(float const*, ...)", "fft_fwd_a"),
     ("void nsg::k_pass_b<512, 8, false>(...)", "fft_fwd_b"),
     ("void nsg::k_pass_b<512, 8, true>(...)", "fft_inv_b"),
-    ("void nsg::k_inv_a<512, 8>(...)", "fft_inv_a_overlap_add"),
+    ("void nsg::k_inv_a<512, 8, false>(...)", "fft_inv_a_overlap_add"),
+    ("void nsg::k_inv_a<1024, 8, true>(...)", "fft_inv_a_overlap_add"),
     ("void nsg::k_band_analysis<256, 8>(...)", "band_analysis_256x8"),
     ("void nsg::k_band_synthesis<1024, 16>(...)", "band_synthesis_1024x16"),
     ("void nsg::k_big_a<512, 8>(nsg::BigArgs, ...)", "huge_band_columns"),
-    ("void nsg::k_big_b<512, 8>(nsg::BigArgs, ...)", "huge_band_rows"),
+    ("void nsg::k_big_b<512, 8, 2>(nsg::BigArgs, ...)", "huge_band_rows"),
+    ("void nsg::k_big_b<512, 8, 8>(nsg::BigArgs, ...)", "huge_band_rows"),
+    ("void nsg::k_band_analysis_all<1024, 8>(...)", "band_analysis_all"),
+    ("void nsg::k_band_synthesis_all<1024, 16>(...)", "band_synthesis_all"),
     ("nsg::k_ola(float const*, ...)", "sliced_overlap_add"),
     ("__amd_rocclr_copyBuffer", None),
 ])
