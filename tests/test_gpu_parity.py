@@ -434,7 +434,7 @@ ONE_LAUNCH = [
     ("block256", (22050.0, 110.0, 11025.0, 12, 16384), 19),
     ("block512", (16000.0, 50.0, 8000.0, 24, 50274), 3),
     ("block1024", (44100.0, 40.0, 22050.0, 24, 132300), 2),
-    ("items16k", (44100.0, 40.0, 22050.0, 24, 220500), 1),
+    ("items16k", (44100.0, 40.0, 22050.0, 24, 220500), 3),
     ("bands30", (44100.0, 40.0, 22050.0, 3, 44100), 3),
 ]
 
@@ -458,6 +458,44 @@ def test_one_launch_band_phase_against_oracle(case):
                               to_np(p.analyse(to_gpu(x)))[i].view(np.uint32))
         assert np.array_equal(to_np(p1.synthesise(to_gpu(y[i:i + 1])))[0].view(np.uint32),
                               to_np(p.synthesise(to_gpu(y)))[i].view(np.uint32))
+
+
+def test_short_phase_beside_a_chain_against_oracle():
+    # a short band phase with huge bands: the chain runs on one stream, the
+    # other bands' launch on another. All operators against the oracle, a
+    # signal's bits at 2 and at 8 signals (a long phase: the 16,384-point tier
+    # has a launch of its own there), and the captured round trip
+    args = (48000.0, 40.0, 24000.0, 12, 240000)
+    N, b = args[-1], 2
+    lay = oracle.build_layout(*args)
+    p, p8 = nb.Plan(*args, batch=b), nb.Plan(*args, batch=8)
+    units = lambda pl: [n for n, _ in pl.stage_info(nb.OP_ANALYSE)][2:]
+    chain = ["big_analysis_a", "big_analysis_b", "big_analysis_a2", "big_analysis_b2"]
+    assert units(p) == chain + ["band_analysis_all"]
+    assert units(p8) == chain + ["band_analysis_all", "band_analysis_1024x16"]
+    x, y = workloads.white(N + 15, 8, N), workloads.coeff_cotangent(N + 16, 8, p.n_coeffs)
+    xs = workloads.signal_cotangent(N + 17, b, N)
+    _check_all_ops(p, lay, x[:b], y[:b], xs, mode="fft")
+    xg = to_gpu(x[:b])
+    ce, ye = to_np(p.analyse(xg)), to_np(p.synthesise(to_gpu(y[:b])))
+    assert np.array_equal(to_np(p8.analyse(to_gpu(x)))[:b].view(np.uint32), ce.view(np.uint32))
+    assert np.array_equal(to_np(p8.synthesise(to_gpu(y)))[:b].view(np.uint32), ye.view(np.uint32))
+    xe = to_np(p.synthesise(to_gpu(ce)))
+    c, xr = to_gpu(np.zeros_like(ce)), torch.zeros_like(xg)
+    ws = {op: p.workspace(op) for op in (nb.OP_ANALYSE, nb.OP_SYNTHESISE)}
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        p.analyse(xg, out=c, ws=ws[nb.OP_ANALYSE])
+        p.synthesise(c, out=xr, ws=ws[nb.OP_SYNTHESISE])
+    for i in range(3):
+        c.zero_()
+        xr.zero_()
+        p.analyse(to_gpu(x[2 + b * i:2 + b * (i + 1)]))
+        torch.cuda.synchronize()
+        g.replay()
+        assert np.array_equal(to_np(c).view(np.uint32), ce.view(np.uint32)), i
+        assert np.array_equal(to_np(xr).view(np.uint32), xe.view(np.uint32)), i
 
 
 def test_erb_layout_against_oracle():
