@@ -118,8 +118,8 @@ struct nsgcqt_plan_s {
     hipStream_t side[kSide] = {};
     hipEvent_t fork_ev = nullptr;
     hipEvent_t join_ev[kSide] = {};
-    // only for plans whose band launches are all small and whose band phase
-    // is long (see schedule)
+    // only for plans with huge bands, or whose band launches are all small and
+    // whose band phase is long (see schedule)
     bool fan = false;
     // launch units: the buckets, then the huge-band chain (when there are huge bands)
     std::vector<int> lane;    // stream of each unit: 0 = caller's
@@ -203,15 +203,16 @@ int upload(nsgcqt_plan_s* p) {
 }
 
 // Launch schedule of the band phase, from the host plan alone. Overlap pays
-// when no band launch fills the GPU by itself and the band phase is long
-// against the fork and join (~25 us each way): the plan's fan flag. Then units
-// are enqueued longest first, each onto the least loaded of the four streams;
-// otherwise in bucket order on the caller's.
+// (about 25 us of fork and join) where there is a huge-band chain, whose
+// dependent launches the others hide behind, and where no band launch fills
+// the GPU by itself and the phase is long: the plan's fan flag. Then units are
+// enqueued longest first by the plan's estimates, each onto the least loaded
+// of the four streams; otherwise in bucket order on the caller's.
 void schedule(nsgcqt_plan_s* p) {
     const HostPlan& h = p->h;
     std::vector<double> cost;
-    for (const auto& bk : h.buckets) cost.push_back(bk.slots);
-    if (!h.bigs.empty()) cost.push_back(4.0 * static_cast<double>(h.Hn) * static_cast<double>(h.batch));
+    for (const auto& bk : h.buckets) cost.push_back(bk.cost);
+    if (!h.bigs.empty()) cost.push_back(h.big_cost);
     p->fan = h.fan && cost.size() > 1;
     p->order.resize(cost.size());
     for (size_t i = 0; i < cost.size(); ++i) p->order[i] = static_cast<int>(i);

@@ -338,6 +338,54 @@ OneFit one_fit(int n, int lg_cap, int ept, int block, int batch, int64_t row_byt
                   stage_cost(rad, n, lg) * (1 << lg) * 64.0 / static_cast<double>(nt) + 2000.0 * rad.size()};
 }
 
+// Estimated duration in us of the transforms of 2^lg sequences of length n by a
+// workgroup of nt threads: the stages' SIMD cycles (see stage_cost; a prime
+// stage's product loop at twice its matrix cycles, it waits for LDS) on the
+// SIMDs that the waves spread over, and 2000 cycles of barriers and round trips
+// a stage, at 2.4 GHz. With 11 us for launch, loads and stores it gives single
+// items of 9,072 to 16,128 points, Bluestein or with primes of 13 to 257, the
+// 20 to 46 us they take alone to 1 us, two of them (35.9, 25.3 us) to 4 us.
+double transform_us(int n, int lg, int nt) {
+    std::vector<int> rad;
+    factor_radices(n, rad);
+    double c = stage_cost(rad, n, lg) * (1 << lg);
+    for (int R : rad)
+        if (R > 16) c += 64.0 * (((R - 1) / 2 + 3) >> 2) * mfma_tiles((n / R) << lg, R);
+    return (c / std::min(4, nt / 64) + 2000.0 * static_cast<double>(rad.size())) / 2400.0;
+}
+
+// Where all bands that are not huge share one launch, it and the huge-band
+// chain are the only units of the schedule. The longer of the two belongs on
+// the caller's stream, for the other starts a fork wait later. Their durations
+// decide, in us: the launch lasts as long as its longest item or as its items'
+// work over 256 compute units, the chain as its passes one after the other. On
+// 39 plans (17 to 493 bands, 1 to 4 signals) the order that they pick is at most
+// 1 % behind the other one, on 12 more at most 6 % (30 bands, 1 x 132,300: 129.6
+// us a round trip, 122.2 with the chain first) and mostly up to 13 % ahead of
+// it. Element slots, as the schedule counts other plans, miss bands with large
+// primes: 1 x 1,000,000 samples from 40 Hz at 48 kHz and 48 bands per octave,
+// whose band of 14,135 = 257 * 11 * 5 points takes 46 us, 177.0 us with the chain
+// first, 166.1 with the launch.
+void unit_durations(HostPlan& p) {
+    Bucket& bk = p.buckets[0];
+    double longest = 0.0, work = 0.0;
+    for (const WorkItem& w : p.items) {
+        const double t = transform_us(w.bd.n, w.lgnb, w.nt) * (w.bd.chirp >= 0 ? 2.0 : 1.0);
+        longest = std::max(longest, t);
+        work += t * std::min(4, w.nt / 64) / 4.0;
+    }
+    bk.cost = 11.0 + std::max(longest, work / 256.0);
+    p.big_cost = 0.0;
+    for (int pass = 0; pass < 4; ++pass) {
+        if (p.big_n[pass] == 0) continue;
+        double tile = 0.0;
+        for (const BigDesc& g : p.bigs)
+            if (pass < 2 || p.banddev[g.band].chirp >= 0)
+                tile = std::max(tile, pass % 2 ? transform_us(g.n2, g.lgb, 512) : transform_us(g.n1, g.lga, 512));
+        p.big_cost += 3.6 + tile + 0.012 * p.big_n[pass];
+    }
+}
+
 // How the band phase is launched, from the tiers of its bands (p.buckets) alone.
 // Sets p.fan and returns the largest transform length that goes into the one
 // launch, 0 for one launch per tier, -1 if a band does not fit its tier's LDS.
@@ -955,14 +1003,12 @@ int finish_plan(HostPlan& p, std::string& err) {
     auto add_items = [&](Bucket& bk, int32_t l, int lg, int nt) {
         const int n = work[l], G = 1 << lg;
         bk.lds_elems = std::max(bk.lds_elems, lds_slots(n, lg));
-        // A shared launch's items count with their own threads. Counted with its
-        // block's, a launch of many one-wave items passed for longer than the
-        // huge-band chain, which was then forked off behind it (1 x 1,000,000 at
-        // 48 bands per octave 168.4 us a round trip, 162.2 by the items' threads).
-        // Counted with its elements alone it falls behind the 16,384-point tier,
-        // which costs more than it should (8 x 240,000 at 12 bands per octave
-        // 202 -> 212 us, 4 x 500,000 at 24 225 -> 237 us, 1 x 2,880,000 319 -> 325).
-        bk.slots += static_cast<double>((batch + G - 1) / G) * (static_cast<double>(nt) * bk.ept);
+        // counted with the threads of the launch's block, so that a shared launch goes
+        // ahead of the 16,384-point tier: by its items' own threads it falls behind
+        // on some plans (4 x 1,091,502 samples from 300 Hz at 22.05 kHz and 48 bands
+        // per octave 382.7 -> 391.6 us, 8 x 667,184 from 20 Hz at 44.1 kHz and 30
+        // 472 -> 482 us), by its elements on more (4 x 500,000 at 24 225 -> 237 us)
+        bk.cost += static_cast<double>((batch + G - 1) / G) * (static_cast<double>(bk.nt) * bk.ept);
         // fast load phases (WorkItem flags): every read up to entry
         // M - 1 + 3 st of the band stays in the data or the guards
         const auto& hb = p.bands[static_cast<size_t>(l)];
@@ -1042,6 +1088,8 @@ int finish_plan(HostPlan& p, std::string& err) {
         }
         p.big_n[pass] = static_cast<int>(p.bigitems.size()) - p.big_off[pass];
     }
+    p.big_cost = 4.0 * static_cast<double>(p.Hn) * static_cast<double>(batch);
+    if (!p.bigs.empty() && p.buckets.size() == 1 && p.buckets[0].all) unit_durations(p);
     p.big_lds_a = static_cast<int>((big_t4 + big_ea) * 8);
     p.big_lds_b = static_cast<int>(big_eb * 8);
     if (!p.bigs.empty() && (p.big_lds_a > 160 * 1024 || p.big_lds_b > 160 * 1024))

@@ -43,7 +43,7 @@ struct Bucket {
     int item_off = 0;     // first work item of the bucket in HostPlan::items
     int nitems = 0;
     int lds_elems = 0;    // largest data LDS slots over its items
-    double slots = 0.0;   // element slots over its items (the schedule's estimate)
+    double cost = 0.0;    // the schedule's estimate: element slots of its items' threads, or us (see plan.cpp)
     bool all = false;     // bands of several tiers in one launch, each item with its own thread count
 };
 
@@ -91,7 +91,7 @@ struct HostPlan {
     std::vector<float> chirp, kern;         // Bluestein tables
     std::vector<float> slicewin;            // sliced plans: window of length N
     std::vector<Bucket> buckets;
-    bool fan = false;           // long band phase without a launch that fills the GPU (see plan.cpp)
+    bool fan = false;           // the band phase forks: huge bands, or long without a launch that fills the GPU
     std::vector<WorkItem> items;
 
     // huge bands (transform above one workgroup): descriptors, work items of
@@ -99,6 +99,7 @@ struct HostPlan {
     std::vector<BigDesc> bigs;
     std::vector<BigItem> bigitems;
     int big_off[4] = {0, 0, 0, 0}, big_n[4] = {0, 0, 0, 0};
+    double big_cost = 0.0;      // the chain's estimate, in the unit of the buckets' costs
     int64_t Hn = 0;             // complex values per signal in each huge-band buffer
     int64_t C_big = 0;          // coefficients of huge bands
     int64_t Hn_blu = 0;         // part of Hn that belongs to Bluestein bands

@@ -432,35 +432,43 @@ def test_stage_order_follows_the_launch_schedule(lib):
 @pytest.mark.parametrize("fs,fmin,bpo,n,batch,units", [
     (22050.0, 2800.0, 12, 16384, 1, ["all"]),                   # 26 bands
     (44100.0, 40.0, 3, 44100, 8, ["all"]),                      # 30 bands
-    (44100.0, 40.0, 3, 132300, 1, ["chain", "all"]),            # 30 bands, huge ones
+    (44100.0, 40.0, 3, 132300, 1, ["all", "chain"]),            # 30 bands, huge ones
     (44100.0, 690.0, 3, 132300, 1, ["chain", "all"]),           # 17 bands, huge ones
     (44100.0, 690.0, 2, 132300, 1, ["chain", "1024x16", "256x16", "512x16", "256x8"]),   # 12 bands
     (22050.0, 5600.0, 12, 16384, 4, ["64x8", "256x8", "1024x16"]),                       # 14 bands
 ])
 def test_launches_of_layouts_with_few_bands(lib, fs, fmin, bpo, n, batch, units):
     # short band phases are one launch from 17 bands on; a huge-band chain
-    # overlaps the other launches (and so goes first) at any number of bands
+    # overlaps the other launches at any number of bands (and so goes first
+    # where it is the longer)
     p = nb.Plan(fs, fmin, fs / 2, bpo, n, batch=batch, device=False)
     names = [x.replace("band_analysis_", "") for x, _ in p.stage_info(nb.OP_ANALYSE)][2:]
     chain = [x for x in names if x.startswith("big_analysis")]
     if chain:
-        assert names[:len(chain)] == chain
-        names = ["chain"] + names[len(chain):]
+        i = names.index(chain[0])
+        assert names[i:i + len(chain)] == chain
+        names[i:i + len(chain)] = ["chain"]
     assert names == units
 
 
-@pytest.mark.parametrize("args,batch,rest", [
-    ((44100.0, 40.0, 22050.0, 48, 1000000), 1, ["all"]),
-    ((48000.0, 40.0, 24000.0, 12, 240000), 1, ["all"]),
-    ((48000.0, 40.0, 24000.0, 12, 240000), 8, ["all", "1024x16"]),
-    ((48000.0, 20.0, 24000.0, 96, 2880000), 1, ["all", "1024x16"]),
+CHAIN = ["big_analysis_a", "big_analysis_b", "big_analysis_a2", "big_analysis_b2"]
+
+
+@pytest.mark.parametrize("args,batch,units", [
+    ((44100.0, 40.0, 22050.0, 48, 1000000), 1, ["chain", "all"]),
+    ((48000.0, 40.0, 24000.0, 48, 1000000), 1, ["all", "chain"]),      # a band of 257 * 11 * 5 points
+    ((48000.0, 40.0, 24000.0, 12, 240000), 1, ["all", "chain"]),       # a chain of 74 workgroups a pass
+    ((48000.0, 40.0, 24000.0, 12, 240000), 4, ["chain", "all"]),
+    ((44100.0, 32.7, 22050.0, 36, 600000), 1, ["all", "chain"]),
+    ((44100.0, 40.0, 22050.0, 24, 500000), 3, ["chain", "all"]),
+    ((48000.0, 40.0, 24000.0, 12, 240000), 8, ["chain", "all", "1024x16"]),
+    ((48000.0, 20.0, 24000.0, 96, 2880000), 1, ["chain", "all", "1024x16"]),
 ])
-def test_huge_band_chain_is_enqueued_before_the_shared_launch(lib, args, batch, rest):
-    # the huge-band chain (four launches in series) is the longest unit of
-    # these plans, ahead of the launch that the smaller tiers share
+def test_longer_of_the_chain_and_the_shared_launch_goes_first(lib, args, batch, units):
+    # a huge-band chain (four launches in series) and the launch that the other
+    # bands share: the longer one is enqueued first, on the caller's stream
     names = [n for n, _ in nb.Plan(*args, batch=batch, device=False).stage_info(nb.OP_ANALYSE)][2:]
-    assert names == ["big_analysis_a", "big_analysis_b", "big_analysis_a2", "big_analysis_b2"] + \
-        ["band_analysis_" + r for r in rest]
+    assert names == sum([CHAIN if u == "chain" else ["band_analysis_" + u] for u in units], [])
 
 
 def test_sliced_stage_info_lists_one_chunk(lib):
