@@ -279,7 +279,13 @@ template <> struct Dft<16> { __device__ __forceinline__ static void run(float2* 
 // ahead, twiddle reads ahead of the input reads and Bluestein's product
 // inside the second transform took the smallest analysis (1 x 16,384) from
 // 32.8 to 28.5 us, 3 x 50,274 from 119 to 107.5 us a round trip and 128 x
-// 88,200 from 377 to 354 us.
+// 88,200 from 377 to 354 us. Taken out one at a time from the kernels as they
+// are now: twiddles read after the inputs 18.9 -> 19.1 and 49.9 -> 50.2 us, an
+// ERB analysis (8 x 64,000) 36.6 -> 37.2, 128 x 88,200 equal; the product in a
+// pass of its own 18.9 -> 19.3, 49.9 -> 50.3, 36.6 -> 36.9 and 348 -> 356 us;
+// a record read at its stage's start 18.8 -> 19.1 and 347 -> 349 us, but 50.0
+// -> 49.4 and 36.4 -> 35.9. What is left of the gain is the divisors. Fixed
+// contraction costs nothing measurable (all within 0.5 %).
 template <int R, int EPT, bool PRE, class NT>
 __device__ __forceinline__ void stage_fixed(float2* buf, NT nt, const StageRec& st, int S, int lgnb,
                                             const float2* __restrict__ tws, const float2* __restrict__ pre,

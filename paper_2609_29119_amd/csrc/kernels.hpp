@@ -27,7 +27,10 @@ namespace nsg {
 #define NSG_OCC_BAND __attribute__((amdgpu_waves_per_eu(((NT == 256 || NT == 64) && EPT == 8) ? 6 : 2)))
 
 // The overlap-add pass waits on its gather: six waves per SIMD there too (at
-// 86 VGPRs and five it took 52.4 us instead of 48.3 on 128 x 88,200).
+// 86 VGPRs and five it took 52.4 us instead of 48.3 on 128 x 88,200). A block
+// of 1024 threads is four waves per SIMD and does not fit twice at 80 VGPRs;
+// the cap costs it nothing (4 x 2,880,000 samples 627 us a synthesis, 632
+// without it, 16 x 1,000,000, 8 x 1,323,000 and 1 x 11,520,000 equal).
 #define NSG_OCC_INV __attribute__((amdgpu_waves_per_eu(6)))
 
 // The kernels' arguments lie in memory, the tables behind a kernel's own. A band
@@ -872,10 +875,11 @@ constexpr int kBigInRoute = 0, kBigInCoef = 1, kBigInBlu2 = 2;
 // grid is little more than the GPU holds at once, so the passes last as long as
 // that chain. The record therefore carries the band, inputs are read four or
 // eight elements at a time ahead of their use, and the rows past the band's
-// length (half of a Bluestein transform) are cleared without reads. One element
-// at a time, with the band's records read one after the other, the round trip
-// of 1 x 2,880,000 took 341 us against 327, 3 x 1,000,000 333 against 320 and
-// 1 x 2,000,000 310 against 297.
+// length (half of a Bluestein transform) are cleared without reads. Before these
+// three the round trip of 1 x 2,880,000 took 341 us against 327, 3 x 1,000,000
+// 333 against 320 and 1 x 2,000,000 310 against 297, repeated on one input.
+// Reading one element at a time alone costs 1 x 2,880,000 324 us against 320
+// and leaves 1 x 1,000,000 at 48 bands per octave within 1 %.
 template <int NT, int EPT>
 __global__ __launch_bounds__(NT) NSG_OCC void k_big_a(BigArgs a, Tables T, int item0, int nitems, int batch,
                                                       int in_mode) {

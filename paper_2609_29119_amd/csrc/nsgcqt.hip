@@ -513,11 +513,14 @@ int run_big(nsgcqt_plan_s* p, BigArgs a, int batch, hipStream_t s) {
     if (h.bigs.empty()) return NSGCQT_OK;
     const int in0 = a.analysis ? kBigInRoute : kBigInCoef;
     // At seven waves per SIMD (70 registers) the row pass holds three workgroups
-    // per compute unit; a larger grid would leave a nearly empty second round, so
-    // it takes the kernel at eight waves and four workgroups (round trips of
-    // 1 x 2,880,000 327 -> 319 us, 3 x 1,000,000 320 -> 316 us, 1 x 2,000,000
-    // 297 -> 292 us; 1 x 1,000,000, fewer workgroups, 170 us at seven and 172
-    // at eight). The column pass spills at eight.
+    // per compute unit, at eight four. Large grids gain from the fourth: round
+    // trips of 500,000 samples at 24 bands per octave with 1,305, 1,450, 1,740,
+    // 2,030 and 2,320 workgroups 381 -> 377, 407 -> 399, 446 -> 434, 506 -> 495
+    // and 554 -> 545 us. From 725 to 1,240 the kernels differ by -1.7 to +1.0 %
+    // without an order (725: 265 -> 261 us, 870: 266 -> 262, 992: 295 -> 297,
+    // 1,160: 331 -> 332; 875 and 959 of 1 x 2,880,000 326 -> 321), and up to
+    // 580 by less than 1 %; the line lies where the fourth workgroup is first
+    // used. The column pass spills at eight.
     constexpr int kThreePerCu = 3 * 256;
     for (int pass = 0; pass < 4; ++pass) {
         const int n = h.big_n[pass];

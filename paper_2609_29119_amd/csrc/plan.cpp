@@ -393,21 +393,29 @@ void unit_durations(HostPlan& p) {
 //    as its longest one (10 to 30 us) however few they are, and the tiers'
 //    launches of a call wait for each other: 3 x 50,274 samples at 24 bands
 //    per octave 105 -> 49 us a round trip, 1 x 220,500 221 -> 85 us, 32 x
-//    88,200 at 36 bands per octave (2.8M coefficients) 157 -> 135 us.
+//    88,200 at 36 bands per octave (2.8M coefficients) 157 -> 135 us. The
+//    16,384-point tier joins it whatever the number of items, though each
+//    workgroup then reserves its LDS: 4, 8 and 10 x 220,500 at 24 bands per
+//    octave take 115, 171 and 198 us with it, 164, 190 and 203 us with the tier
+//    in a launch of its own, 186, 205 and 217 us with every tier on its own
+//    stream; 8 and 12 x 220,500 at 36 178, 199, 205 and 233, 248, 223 us; 32 x
+//    88,200 at 12 210, 213 and 220 us.
 //  - From kLongPhase on the launches fill the GPU or nearly do, and a launch
 //    whose workgroups all reserve the largest item's threads and LDS costs more
 //    than the waits: 64 x 88,200 215 us in one launch, 208 us by tier; 48 x
 //    177 and 183 us.
 //  - Long phases without a launch that fills the GPU fan out over streams
-//    (see the schedule), and so does a huge-band chain with its neighbour
-//    launch: 1 x 1,000,000 at 48 bands per octave 202 -> 173 us. Merging the
-//    tiers there as well moves 16 x 220,500 236 -> 229 to 246 us and 24 x
-//    220,500 at 36 bands per octave 265 -> 283 to 362 us by how much is merged.
-//  - Beside a huge-band chain, which is the longest of their units, the tiers
-//    share one launch: two forks fewer (1 x 2,880,000 365 -> 341 us, 6 x
-//    500,000 285 -> 270 us). The 16,384-point tier joins it for up to two
-//    items per compute unit, since every workgroup then reserves 128 KB of LDS
-//    (1 x 2,000,000 284 -> 270 us; beyond, 3 x 1,000,000 300 -> 309 us).
+//    (see the schedule): 16 x 220,500 282 us in series, 235 us. Merging the
+//    tiers there as well moves that to 229 to 246 us and 24 x 220,500 at 36
+//    bands per octave 265 -> 283 to 362 us by how much is merged.
+//  - A huge-band chain overlaps the other launches at any length: 1 x 1,000,000
+//    at 48 bands per octave 199 us in series, 162 us; 6 x 500,000 303 and 262
+//    us; 1 x 2,880,000 418 and 320 us; 1 x 240,000 156 and 128 us. Beside it the
+//    tiers share one launch, two forks fewer (measured when that was done: 1 x
+//    2,880,000 365 -> 341 us, 6 x 500,000 285 -> 270 us). The 16,384-point tier
+//    joins it for up to two items per compute unit, since every workgroup then
+//    reserves 128 KB of LDS (then 1 x 2,000,000 284 -> 270 us; beyond, 3 x
+//    1,000,000 300 -> 309 us).
 //  - Plans of up to 16 bands keep a launch per tier. Speed does not draw this
 //    line: one launch is the faster form down to the smallest layouts measured
 //    (28 bands, 1 x 32,000 133 -> 52 us; 24 bands with a chain, 1 x 400,000
